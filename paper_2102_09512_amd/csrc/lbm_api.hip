@@ -52,6 +52,20 @@ int select_device(Ctx* c) {
   return LBM_OK;
 }
 
+// Whether a kernel of handle c may address caller memory p itself: memory of
+// the handle's own device, aligned to its element.  Anything else that a copy
+// accepts (another device's memory, pinned host memory, an odd address) goes
+// through a staging buffer.
+bool direct(const Ctx* c, const void* p, size_t element) {
+  if ((uintptr_t)p % element) return false;
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == c->device;
+}
+
 int ensure_scratch(Ctx* c) {
   if (!c->fields) {
     HIP_OR_FAIL(hipMalloc(&c->fields, sizeof(double) * 6 * (size_t)c->N), "hipMalloc(fields)");
@@ -523,6 +537,10 @@ int lbm_get_state(lbm_handle h, void* buf, size_t bytes, int mem) {
   if (bytes != lbm_state_bytes(h)) return fail(LBM_EINVAL, "lbm_get_state: wrong buffer size");
   int rc = select_device(c);
   if (rc) return rc;
+  if (mem == LBM_DEVICE && direct(c, buf, word_of(c->precision))) {
+    HIP_OR_FAIL(lbm::launch_pack(*c, c->buf[c->cur], buf), "pack kernel");
+    return LBM_OK;
+  }
   // pack into the other population buffer (its content is dead between steps), then copy out
   void* scratch = c->buf[c->cur ^ 1];
   HIP_OR_FAIL(lbm::launch_pack(*c, c->buf[c->cur], scratch), "pack kernel");
@@ -541,10 +559,14 @@ int lbm_set_state(lbm_handle h, const void* buf, size_t bytes, int mem, int64_t 
   if (bytes != lbm_state_bytes(h)) return fail(LBM_EINVAL, "lbm_set_state: wrong buffer size");
   int rc = select_device(c);
   if (rc) return rc;
-  HIP_OR_FAIL(hipMemcpyAsync(c->buf[1], buf, bytes, mem == LBM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
-                             c->stream),
-              "copy state");
-  HIP_OR_FAIL(lbm::launch_unpack(*c, c->buf[1], c->buf[0]), "unpack kernel");
+  const void* state = buf;
+  if (mem == LBM_HOST || !direct(c, buf, word_of(c->precision))) {
+    HIP_OR_FAIL(hipMemcpyAsync(c->buf[1], buf, bytes,
+                               mem == LBM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, c->stream),
+                "copy state");
+    state = c->buf[1];
+  }
+  HIP_OR_FAIL(lbm::launch_unpack(*c, state, c->buf[0]), "unpack kernel");
   if (mem == LBM_HOST) HIP_OR_FAIL(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
   c->cur = 0;
   c->step = step;
