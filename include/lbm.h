@@ -161,15 +161,13 @@ int lbm_moments(lbm_handle h, double* rho, double* u, double* T, int mem);
    *out (host): the totals of Eqs. (3)-(5) and the statistics of Sec. III.D
    listed at lbm_diag.  Sets the handle's instability flag when a node is
    non-finite or has rho <= 0 or T <= 0 (lbm_step then returns
-   LBM_EUNSTABLE).  Allocates a 6 N-double field buffer and the partial sums
-   on first use.  LBM_EINVAL on a NULL argument, LBM_ESTATE before
+   LBM_EUNSTABLE).  Allocates the partial sums on first use.  LBM_EINVAL on a NULL argument, LBM_ESTATE before
    lbm_init_fields. */
 int lbm_diagnostics(lbm_handle h, lbm_diag* out);
 /* lbm_diagnostics for callers that cannot allocate device memory (code
    under HIP graph capture, tight serving loops, harnesses that forbid
-   hipMalloc): the same sums into *out (host), formed straight from the
-   stored populations by the same arithmetic over the same grid, with no
-   field buffer and no allocation.  The block partial sums and the final
+   hipMalloc): the same sums into *out (host), by the same kernel over the
+   same grid, with no allocation.  The block partial sums and the final
    sums live in a library-owned device array of 2048 x 21 + 21 doubles
    (344 KB) on each device, obtained at lbm_create and held until the
    process ends; it covers any grid lbm_create accepts (at most 2048

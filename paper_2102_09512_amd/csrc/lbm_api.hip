@@ -66,16 +66,17 @@ bool direct(const Ctx* c, const void* p, size_t element) {
   return a.type == hipMemoryTypeDevice && a.device == c->device;
 }
 
-int ensure_scratch(Ctx* c) {
-  if (!c->fields) {
-    HIP_OR_FAIL(hipMalloc(&c->fields, sizeof(double) * 6 * (size_t)c->N), "hipMalloc(fields)");
-  }
+int ensure_fields(Ctx* c) {
+  if (!c->fields) HIP_OR_FAIL(hipMalloc(&c->fields, sizeof(double) * 5 * (size_t)c->N), "hipMalloc(fields)");
+  return LBM_OK;
+}
+
+int ensure_partials(Ctx* c) {
   if (!c->partial) {
-    c->partial_blocks = lbm::diag_blocks(*c);
-    HIP_OR_FAIL(hipMalloc(&c->partial, sizeof(double) * lbm::kNumDiag * (size_t)c->partial_blocks),
-                "hipMalloc(partial)");
-    HIP_OR_FAIL(hipMalloc(&c->diag_dev, sizeof(double) * lbm::kNumDiag), "hipMalloc(diag)");
+    const size_t diag = (size_t)lbm::kNumDiag * lbm::diag_grid(*c).blocks, validate = lbm::validate_blocks(*c);
+    HIP_OR_FAIL(hipMalloc(&c->partial, sizeof(double) * (diag > validate ? diag : validate)), "hipMalloc(partial)");
   }
+  if (!c->diag_dev) HIP_OR_FAIL(hipMalloc(&c->diag_dev, sizeof(double) * lbm::kNumDiag), "hipMalloc(diag)");
   return LBM_OK;
 }
 
@@ -227,7 +228,7 @@ int lbm::fields_current(lbm::Ctx* base) {
   if (!c->initialised) return fail(LBM_ESTATE, "corrector: no state (lbm_init_fields)");
   int rc = ::select_device(c);
   if (rc) return rc;
-  if ((rc = ::ensure_scratch(c))) return rc;
+  if ((rc = ::ensure_fields(c))) return rc;
   HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], c->fields), "moments kernel");
   return LBM_OK;
 }
@@ -398,11 +399,11 @@ int lbm_init_fields(lbm_handle h, const double* rho, const double* u, const doub
   if (rc) return rc;
   const int64_t N = c->N;
   const int D = c->lattice;
-  if ((rc = ensure_scratch(c))) return rc;
   const double *drho = rho, *du = u, *dT = T;
   if (mem == LBM_HOST) {
     if (!fields_valid_host(rho, u, T, N, D))
       return fail(LBM_EINVAL, "lbm_init_fields: non-finite value or rho <= 0 or T <= 0");
+    if ((rc = ensure_fields(c))) return rc;
     double* F = c->fields;
     HIP_OR_FAIL(hipMemcpyAsync(F, rho, sizeof(double) * N, hipMemcpyHostToDevice, c->stream), "copy rho");
     HIP_OR_FAIL(hipMemcpyAsync(F + N, u, sizeof(double) * N * D, hipMemcpyHostToDevice, c->stream), "copy u");
@@ -411,7 +412,8 @@ int lbm_init_fields(lbm_handle h, const double* rho, const double* u, const doub
     du = F + N;
     dT = F + 4 * N;
   } else {
-    HIP_OR_FAIL(lbm::launch_validate(*c, rho, u, T, c->partial, c->partial_blocks, c->diag_dev), "validate");
+    if ((rc = ensure_partials(c))) return rc;
+    HIP_OR_FAIL(lbm::launch_validate(*c, rho, u, T, c->partial, lbm::validate_blocks(*c), c->diag_dev), "validate");
     double bad = 0.0;
     HIP_OR_FAIL(hipMemcpyAsync(&bad, c->diag_dev, sizeof(double), hipMemcpyDeviceToHost, c->stream), "copy count");
     HIP_OR_FAIL(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
@@ -462,7 +464,13 @@ int lbm_moments(lbm_handle h, double* rho, double* u, double* T, int mem) {
   if (!c->initialised) return fail(LBM_ESTATE, "lbm_moments: call lbm_init_fields first");
   int rc = select_device(c);
   if (rc) return rc;
-  if ((rc = ensure_scratch(c))) return rc;
+  auto straight = [c](const void* q) { return !q || direct(c, q, sizeof(double)); };
+  if (mem == LBM_DEVICE && straight(rho) && straight(u) && straight(T)) {
+    if (rho || u || T)
+      HIP_OR_FAIL(lbm::launch_moments(*c, c->buf[c->cur], rho, u, c->lattice, T), "moments kernel");
+    return LBM_OK;
+  }
+  if ((rc = ensure_fields(c))) return rc;
   const int64_t N = c->N;
   HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], c->fields), "moments kernel");
   const hipMemcpyKind kind = mem == LBM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
@@ -479,9 +487,9 @@ int lbm_diagnostics(lbm_handle h, lbm_diag* out) {
   if (!c->initialised) return fail(LBM_ESTATE, "lbm_diagnostics: call lbm_init_fields first");
   int rc = select_device(c);
   if (rc) return rc;
-  if ((rc = ensure_scratch(c))) return rc;
-  HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], c->fields), "moments kernel");
-  HIP_OR_FAIL(lbm::launch_diag(*c, c->fields, c->partial, c->partial_blocks, c->diag_dev), "diagnostics kernel");
+  if ((rc = ensure_partials(c))) return rc;
+  HIP_OR_FAIL(lbm::launch_diag(*c, c->buf[c->cur], c->partial, lbm::diag_grid(*c), c->diag_dev),
+              "diagnostics kernel");
   double v[lbm::kNumDiag];
   HIP_OR_FAIL(hipMemcpyAsync(v, c->diag_dev, sizeof v, hipMemcpyDeviceToHost, c->stream), "copy diagnostics");
   HIP_OR_FAIL(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
@@ -495,13 +503,13 @@ int lbm_diagnostics_noalloc(lbm_handle h, lbm_diag* out) {
   if (!c->initialised) return fail(LBM_ESTATE, "lbm_diagnostics_noalloc: call lbm_init_fields first");
   int rc = select_device(c);
   if (rc) return rc;
-  const int nblocks = lbm::diag_blocks(*c);
-  if (nblocks < 1 || nblocks > lbm::kMaxDiagBlocks)
+  const lbm::DiagGrid g = lbm::diag_grid(*c);
+  if (g.blocks < 1 || g.blocks > lbm::kMaxDiagBlocks)
     return fail(LBM_EINVAL, "lbm_diagnostics_noalloc: the reduction needs more partial sums than the scratch holds");
   double* sc = nullptr;
   if ((rc = scratch_for_device(c->device, &sc))) return rc;
   double* final_sums = sc + (size_t)lbm::kMaxDiagBlocks * lbm::kNumDiag;
-  HIP_OR_FAIL(lbm::launch_diag_direct(*c, c->buf[c->cur], sc, nblocks, final_sums), "diagnostics kernel");
+  HIP_OR_FAIL(lbm::launch_diag(*c, c->buf[c->cur], sc, g, final_sums), "diagnostics kernel");
   double v[lbm::kNumDiag];
   HIP_OR_FAIL(hipMemcpyAsync(v, final_sums, sizeof v, hipMemcpyDeviceToHost, c->stream), "copy diagnostics");
   HIP_OR_FAIL(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
@@ -586,7 +594,7 @@ static int fields_update(lbm_handle h, const double* drho, const double* du, con
   if (!c->initialised) return fail(LBM_ESTATE, std::string(name) + ": no state (lbm_init_fields)");
   int rc = select_device(c);
   if (rc) return rc;
-  if ((rc = ensure_scratch(c))) return rc;
+  if ((rc = ensure_fields(c)) || (rc = ensure_partials(c))) return rc;
   const int64_t N = c->N;
   const int D = c->lattice;
   if (!c->work) HIP_OR_FAIL(hipMalloc(&c->work, sizeof(double) * 10 * (size_t)N), "hipMalloc(work)");
@@ -602,7 +610,8 @@ static int fields_update(lbm_handle h, const double* drho, const double* du, con
   }
   HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], c->fields), "moments kernel");
   HIP_OR_FAIL(lbm::launch_fields_plus(*c, c->fields, drho, du, dT, newf, keep), "increment kernel");
-  HIP_OR_FAIL(lbm::launch_validate(*c, newf, newf + N, newf + 4 * N, c->partial, c->partial_blocks, c->diag_dev),
+  HIP_OR_FAIL(lbm::launch_validate(*c, newf, newf + N, newf + 4 * N, c->partial, lbm::validate_blocks(*c),
+                                   c->diag_dev),
               "validate");
   double bad = 0.0;
   HIP_OR_FAIL(hipMemcpyAsync(&bad, c->diag_dev, sizeof(double), hipMemcpyDeviceToHost, c->stream), "copy count");
@@ -631,7 +640,6 @@ int lbm_filter_moments(lbm_handle h, int factor, double* rho, double* u, double*
     return fail(LBM_EINVAL, "lbm_filter_moments: dims not divisible by the factor");
   int rc = select_device(c);
   if (rc) return rc;
-  if ((rc = ensure_scratch(c))) return rc;
   const int64_t Nc = (c->n[0] / factor) * (c->n[1] / factor) * (D == 3 ? c->n[2] / factor : 1);
   double *r = rho, *v = u, *t = T;
   if (mem == LBM_HOST) {
@@ -640,8 +648,7 @@ int lbm_filter_moments(lbm_handle h, int factor, double* rho, double* u, double*
     v = r + Nc;
     t = v + 3 * Nc;
   }
-  HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], c->fields), "moments kernel");
-  HIP_OR_FAIL(lbm::launch_filter(*c, c->fields, factor, r, v, t), "filter kernel");
+  HIP_OR_FAIL(lbm::launch_filter(*c, c->buf[c->cur], factor, r, v, t), "filter kernel");
   if (mem == LBM_HOST) {
     HIP_OR_FAIL(hipMemcpyAsync(rho, r, sizeof(double) * Nc, hipMemcpyDeviceToHost, c->stream), "copy rho");
     HIP_OR_FAIL(hipMemcpyAsync(u, v, sizeof(double) * Nc * D, hipMemcpyDeviceToHost, c->stream), "copy u");

@@ -72,11 +72,10 @@ struct Ctx {
   Tile tile{};
   void* buf[2] = {nullptr, nullptr}; // population buffers (2Q x ps elements each)
   int cur = 0;                       // buffer holding the current state
-  double* fields = nullptr;          // 6 x N doubles: rho, ux, uy, uz, T, rhoE
+  double* fields = nullptr;          // 5 x N doubles, on first use: rho, ux, uy, uz, T
   double* work = nullptr;            // 10 x N doubles, on first use: new fields and staged increments
   double* partial = nullptr;         // per-block partial sums
   double* diag_dev = nullptr;        // final sums
-  int partial_blocks = 0;
   bool initialised = false;
   bool unstable = false;
   int64_t step = 0;
@@ -88,6 +87,13 @@ constexpr int kMaxDiagBlocks = 2048;  // work-groups of a diagnostic reduction, 
 // doubles of the allocation-free diagnostics' device scratch: the block
 // partials of the largest grid, then the final sums
 constexpr int kScratchDoubles = kMaxDiagBlocks * kNumDiag + kNumDiag;
+
+// Launch geometry of the diagnostics: `tasks` tiles times march chunks dealt
+// out over `blocks` work-groups.
+struct DiagGrid {
+  int by;  // y width of the tile (D3Q27)
+  int tiles_x, tiles_y, chunk, tasks, blocks;
+};
 
 // One box of a batched launch (an entry of the device box table).
 struct BoxEntry {
@@ -119,14 +125,18 @@ hipError_t launch_step(const Ctx& c, const void* src, void* dst);
 // The step kernel's access pattern without the node arithmetic (measurement).
 hipError_t launch_pattern(const Ctx& c, const void* src, void* dst);
 hipError_t launch_init(const Ctx& c, const double* rho, const double* u, const double* T, void* dst);
+// Moments of the stored state into rho[N], u[nu planes of N], T[N] (any may be
+// NULL), and into the field buffer (rho, three u planes, T).
+hipError_t launch_moments(const Ctx& c, const void* pops, double* rho, double* u, int nu, double* T);
 hipError_t launch_fields(const Ctx& c, const void* pops, double* fields);
-hipError_t launch_diag(const Ctx& c, const double* fields, double* partial, int nblocks, double* out);
-// The same sums straight from the populations (no field buffer), and the
-// device address of the current device's allocation-free scratch
+// The diagnostic sums from the populations: g.blocks partials of each sum,
+// then the sums (kNumDiag, in diag_from_sums' order).
+hipError_t launch_diag(const Ctx& c, const void* pops, double* partial, const DiagGrid& g, double* out);
+DiagGrid diag_grid(const Ctx& c);
+// Device address of the current device's allocation-free scratch
 // (kScratchDoubles doubles).
-hipError_t launch_diag_direct(const Ctx& c, const void* pops, double* partial, int nblocks, double* out);
 hipError_t scratch_address(double** out);
-int diag_blocks(const Ctx& c);
+int validate_blocks(const Ctx& c);
 hipError_t launch_validate(const Ctx& c, const double* rho, const double* u, const double* T, double* partial,
                            int nblocks, double* out);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
@@ -138,7 +148,7 @@ int set_error(int code, const std::string& msg);
 hipError_t launch_fields_add(const Ctx& c, void* pops, const double* oldf, const double* newf);
 hipError_t launch_fields_plus(const Ctx& c, const double* oldf, const double* drho, const double* du, const double* dT,
                               double* newf, bool keep);
-hipError_t launch_filter(const Ctx& c, const double* fields, int factor, double* rho, double* u, double* T);
+hipError_t launch_filter(const Ctx& c, const void* pops, int factor, double* rho, double* u, double* T);
 // Corrector support (host, lbm_api.hip): moments into c->fields; increments
 // applied by re-equilibration, asynchronously and without validation.
 int fields_current(Ctx* c);

@@ -678,23 +678,28 @@ __global__ void __launch_bounds__(256) init_kernel(const double* __restrict__ rh
 // fields: rho, ux, uy, uz, T, rhoE (each N)
 // ---------------------------------------------------------------------------
 
-// Sums of the stored values of node n: s0 = sum f, j = sum c f and, when se
-// is not NULL, *se = sum g (in population order).
+// The Q (f, g) pairs of the node whose slot-0 pair is at src.
 template <int D, typename S>
-__device__ inline void stored_sums(const S* __restrict__ pops, const StepParams& p, long long n, double& s0,
-                                   double* j, double* se) {
-  constexpr int Q = lat_q(D);
+__device__ inline void load_pairs(const S* __restrict__ src, const StepParams& p, typename Buf<S>::pair_t* v) {
+#pragma unroll
+  for (int i = 0; i < lat_q(D); ++i) v[i] = *(const typename Buf<S>::pair_t*)(src + i * p.sl);
+}
+
+// Sums of a node's stored values: s0 = sum f, j = sum c f and, when se is not
+// NULL, *se = sum g (in population order).
+template <int D, typename P>
+__device__ inline void pair_sums(const P* v, double& s0, double* j, double* se) {
   double jx = 0, jy = 0, jz = 0, e = 0;
   s0 = 0;
 #pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const double v = (double)pops[pop_offset(p, Q, i, n)];
-    s0 += v;
-    if (se) e += (double)pops[pop_offset(p, Q, i + Q, n)];
+  for (int i = 0; i < lat_q(D); ++i) {
+    const double w = (double)v[i].x;
+    s0 += w;
+    if (se) e += (double)v[i].y;
     const int cx = vx(i), cy = vy(i), cz = (D == 3) ? vz(i) : 0;
-    if (cx) jx += cx > 0 ? v : -v;
-    if (cy) jy += cy > 0 ? v : -v;
-    if (cz) jz += cz > 0 ? v : -v;
+    if (cx) jx += cx > 0 ? w : -w;
+    if (cy) jy += cy > 0 ? w : -w;
+    if (cz) jz += cz > 0 ? w : -w;
   }
   j[0] = jx;
   j[1] = jy;
@@ -702,11 +707,9 @@ __device__ inline void stored_sums(const S* __restrict__ pops, const StepParams&
   if (se) *se = e;
 }
 
-// rho and u of node n from its stored populations (FP64).
-template <int D, typename S>
-__device__ inline double stored_velocity(const S* __restrict__ pops, const StepParams& p, long long n, double* u) {
-  double s0, j[3];
-  stored_sums<D, S>(pops, p, n, s0, j, nullptr);
+// rho and u of a node from the sums of its stored populations (FP64).
+template <int D>
+__device__ inline double velocity_of(const StepParams& p, double s0, const double* j, double* u) {
   const double rho = p.rho0 + s0;
   u[0] = (p.j0[0] + j[0]) / rho;
   u[1] = (p.j0[1] + j[1]) / rho;
@@ -714,45 +717,47 @@ __device__ inline double stored_velocity(const S* __restrict__ pops, const StepP
   return rho;
 }
 
-// rho, u, T and rho E of node n from its stored populations (FP64; Eqs.
-// (3)-(7) without streaming).
-template <int D, typename S>
-__device__ inline void stored_fields(const S* __restrict__ pops, const StepParams& p, long long n, double& rho,
-                                     double* u, double& T, double& rhoE) {
-  double s0, j[3], se;
-  stored_sums<D, S>(pops, p, n, s0, j, &se);
-  rho = p.rho0 + s0;
-  u[0] = (p.j0[0] + j[0]) / rho;
-  u[1] = (p.j0[1] + j[1]) / rho;
-  u[2] = (D == 3) ? (p.j0[2] + j[2]) / rho : 0.0;
+// rho, u, T and rho E of a node from the sums of its stored populations (FP64;
+// Eqs. (3)-(7) without streaming).
+template <int D>
+__device__ inline void fields_of(const StepParams& p, double s0, const double* j, double se, double& rho, double* u,
+                                 double& T, double& rhoE) {
+  rho = velocity_of<D>(p, s0, j, u);
   rhoE = p.rhoE0 + se;
   const double e = rhoE / rho - 0.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);  // U(T)
   T = p.caloric ? p.T0 + caloric_step(p.Cv, p.cv1, p.cv2, p.T0, e - p.U0) : e * p.inv_Cv;
 }
 
-template <int D, bool DEV, typename S>
-__global__ void __launch_bounds__(256) fields_kernel(const S* __restrict__ pops, double* __restrict__ fields,
-                                                     long long N, const StepParams p) {
-  const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+// Any of rho, u (nu planes) and T may be NULL.  Bound by memory: 2Q values
+// read and D + 2 written per node, straight into the caller's arrays.  A
+// thread reads each (f, g) pair in one access.
+template <int D, typename S>
+__global__ void __launch_bounds__(256) fields_kernel(const S* __restrict__ pops, double* __restrict__ rho_out,
+                                                     double* __restrict__ u_out, int nu, double* __restrict__ T_out,
+                                                     int N, const StepParams p) {
+  const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
-  double rho, u[3], T, rhoE;
-  stored_fields<D, S>(pops, p, n, rho, u, T, rhoE);
-  fields[n] = rho;
-  fields[N + n] = u[0];
-  fields[2 * N + n] = u[1];
-  fields[3 * N + n] = u[2];
-  fields[4 * N + n] = T;
-  fields[5 * N + n] = rhoE;
+  typename Buf<S>::pair_t v[lat_q(D)];
+  load_pairs<D>(pops + pair_offset(p, n), p, v);
+  double s0, j[3], se, rho, u[3], T, rhoE;
+  pair_sums<D>(v, s0, j, &se);
+  fields_of<D>(p, s0, j, se, rho, u, T, rhoE);
+  if (rho_out) rho_out[n] = rho;
+  if (u_out)
+    for (int a = 0; a < nu; ++a) u_out[(long long)a * N + n] = u[a];
+  if (T_out) T_out[n] = T;
 }
 
 // ---------------------------------------------------------------------------
 // Reductions: wave64 shuffles, then LDS across the waves of a block, FP64
-// per-block partials; a one-block pass sums the partials in a fixed order.
+// per-block partials; a second launch, one work-group per sum, adds the
+// partials in a fixed order.
 // ---------------------------------------------------------------------------
 
-template <int NV>
-__device__ inline void block_reduce_store(double (&v)[NV], double* __restrict__ out) {
-  __shared__ double red[NV][4];  // 256 threads = 4 waves
+// The NV sums over a work-group of NW wavefronts; sum j goes to out[j * stride].
+template <int NV, int NW>
+__device__ inline void block_reduce_store(double (&v)[NV], double* __restrict__ out, int stride) {
+  __shared__ double red[NV][NW];
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     double x = v[j];
@@ -768,142 +773,205 @@ __device__ inline void block_reduce_store(double (&v)[NV], double* __restrict__ 
   __syncthreads();
   if (threadIdx.x < NV) {
     const int j = threadIdx.x;
-    out[j] = (red[j][0] + red[j][1]) + (red[j][2] + red[j][3]);
+    double x = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; w += 2) x += red[j][w] + (w + 1 < NW ? red[j][w + 1] : 0.0);
+    out[(long long)j * stride] = x;
   }
 }
 
-__device__ inline int fix_node_axis(int k, int n, int bc) { return fix_coord(k, n, bc); }
-
-// Node indices of the six neighbours x+-1, y+-1, z+-1 of node n (wrap or
-// clamp per axis): nb[0] = x+1, nb[1] = x-1, nb[2] = y+1, nb[3] = y-1,
-// nb[4] = z+1, nb[5] = z-1.
-__device__ inline void neighbours6(const StepParams& p, long long n, long long* nb) {
-  const int nx = p.nx, ny = p.ny, nz = p.nz;
-  const int x = (int)(n % nx);
-  const int y = (int)((n / nx) % ny);
-  const int z = (int)(n / ((long long)nx * ny));
-  auto idx = [&](int xx, int yy, int zz) { return xx + (long long)nx * (yy + (long long)ny * zz); };
-  nb[0] = idx(fix_node_axis(x + 1, nx, p.bc[0]), y, z);
-  nb[1] = idx(fix_node_axis(x - 1, nx, p.bc[0]), y, z);
-  nb[2] = idx(x, fix_node_axis(y + 1, ny, p.bc[1]), z);
-  nb[3] = idx(x, fix_node_axis(y - 1, ny, p.bc[1]), z);
-  nb[4] = idx(x, y, fix_node_axis(z + 1, nz, p.bc[2]));
-  nb[5] = idx(x, y, fix_node_axis(z - 1, nz, p.bc[2]));
-}
-
-// One node's terms of the 21 diagnostic sums (the totals of Eqs. (3)-(5)
-// and the statistics of Sec. III.D), with central differences from the
-// velocities vn[k] of the six neighbours (order of neighbours6).
+// The 21 diagnostic sums: the totals of Eqs. (3)-(5) and the statistics of
+// Sec. III.D.  of_node adds the terms that need one node's fields,
+// of_differences those of the central differences, from the velocities vn[k]
+// of the six neighbours (x + 1, x - 1, y + 1, y - 1, z + 1, z - 1).
 template <int D>
-__device__ inline void diag_accumulate(double (&acc)[kNumDiag], const StepParams& p, double rho, const double* u,
-                                       double T, double rhoE, const double (*vn)[3]) {
-  const double ux = u[0], uy = u[1], uz = u[2];
-  // central differences d_b u_a
-  const double dxux = 0.5 * (vn[0][0] - vn[1][0]);
-  const double dyuy = 0.5 * (vn[2][1] - vn[3][1]);
-  const double dzuz = (D == 3) ? 0.5 * (vn[4][2] - vn[5][2]) : 0.0;
-  const double dxuy = 0.5 * (vn[0][1] - vn[1][1]);
-  const double dyux = 0.5 * (vn[2][0] - vn[3][0]);
-  double wx = 0.0, wy = 0.0;
-  if (D == 3) {
-    wx = 0.5 * (vn[2][2] - vn[3][2]) - 0.5 * (vn[4][1] - vn[5][1]);
-    wy = 0.5 * (vn[4][0] - vn[5][0]) - 0.5 * (vn[0][2] - vn[1][2]);
-  }
-  const double wz = dxuy - dyux;
-  const double vort2 = wx * wx + wy * wy + wz * wz;
-  const double div = dxux + dyuy + dzuz;
-  const double uu = ux * ux + uy * uy + uz * uz;
-  const bool finite = isfinite(rho) && isfinite(T) && isfinite(ux) && isfinite(uy) && isfinite(uz);
-  const double mu = (p.visc_exp == 0.0) ? p.mu0 : p.mu0 * pow(T * p.inv_Tref, p.visc_exp);
-  acc[0] += rho;
-  acc[1] += rho * ux;
-  acc[2] += rho * uy;
-  acc[3] += rho * uz;
-  acc[4] += rhoE;
-  acc[5] += 0.5 * rho * uu;
-  acc[6] += div * div;
-  acc[7] += uu;
-  double gam = p.gamma;  // C_p / C_v at T (Mayer: C_p = C_v + 1)
-  if (p.caloric) {
-    const double cvT = caloric_cv(p.Cv, p.cv1, p.cv2, T);
-    gam = (cvT + 1.0) / cvT;
-  }
-  acc[8] += sqrt(gam * T);
-  acc[9] += rho * rho;
-  acc[10] += vort2;
-  acc[11] += mu * vort2;
-  acc[12] += ux * ux;
-  acc[13] += uy * uy;
-  acc[14] += uz * uz;
-  acc[15] += dxux * dxux;
-  acc[16] += dyuy * dyuy;
-  acc[17] += dzuz * dzuz;
-  acc[18] += finite ? 0.0 : 1.0;
-  acc[19] += (rho <= 0.0 || T <= 0.0) ? 1.0 : 0.0;
-  acc[20] += 1.0;
-}
+struct DiagSums {
+  double mass = 0, mom[3] = {}, energy = 0, kinetic = 0, div2 = 0, cs = 0, rho2 = 0, vort2 = 0, diss = 0;
+  double u2[3] = {}, du2[3] = {};
+  unsigned nonfinite = 0, nonpositive = 0, nodes = 0;  // of one thread
 
-// Diagnostics from the field buffer F (rho, u_x, u_y, u_z, T, rho E planes).
-template <int D>
-__global__ void __launch_bounds__(256) diag_kernel(const double* __restrict__ F, double* __restrict__ partial,
-                                                   long long N, const StepParams p) {
-  double acc[kNumDiag];
-#pragma unroll
-  for (int j = 0; j < kNumDiag; ++j) acc[j] = 0.0;
-  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
-    long long nb[6];
-    neighbours6(p, n, nb);
-    double vn[6][3];
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) vn[k][a] = F[(long long)(1 + a) * N + nb[k]];
-    const double u[3] = {F[N + n], F[2 * N + n], F[3 * N + n]};
-    diag_accumulate<D>(acc, p, F[n], u, F[4 * N + n], F[5 * N + n], vn);
-  }
-  block_reduce_store<kNumDiag>(acc, partial + (long long)blockIdx.x * kNumDiag);
-}
-
-// The same sums straight from the stored populations: every node forms its
-// own fields and its neighbours' velocities from the populations with the
-// arithmetic of fields_kernel, so the terms, and with the same grid the
-// sums, are those of fields_kernel + diag_kernel; no field buffer is needed.
-template <int D, typename S>
-__global__ void __launch_bounds__(256) diag_direct_kernel(const S* __restrict__ pops, double* __restrict__ partial,
-                                                          long long N, const StepParams p) {
-  double acc[kNumDiag];
-#pragma unroll
-  for (int j = 0; j < kNumDiag; ++j) acc[j] = 0.0;
-  for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < N; n += (long long)gridDim.x * blockDim.x) {
-    long long nb[6];
-    neighbours6(p, n, nb);
-    double vn[6][3];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      if (D == 2 && k >= 4) {  // no z neighbours: the (unused) z differences see the node itself
-        vn[k][0] = vn[k][1] = vn[k][2] = 0.0;
-        continue;
-      }
-      stored_velocity<D, S>(pops, p, nb[k], vn[k]);
+  __device__ inline void of_node(const StepParams& p, double rho, const double* u, double T, double rhoE) {
+    const bool finite = isfinite(rho) && isfinite(T) && isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]);
+    mass += rho;
+    energy += rhoE;
+    kinetic += 0.5 * rho * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+    double gam = p.gamma;  // C_p / C_v at T (Mayer: C_p = C_v + 1)
+    if (p.caloric) {
+      const double cvT = caloric_cv(p.Cv, p.cv1, p.cv2, T);
+      gam = (cvT + 1.0) / cvT;
     }
-    double rho, u[3], T, rhoE;
-    stored_fields<D, S>(pops, p, n, rho, u, T, rhoE);
-    diag_accumulate<D>(acc, p, rho, u, T, rhoE, vn);
+    cs += sqrt(gam * T);
+    rho2 += rho * rho;
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      mom[a] += rho * u[a];
+      u2[a] += u[a] * u[a];
+    }
+    nonfinite += finite ? 0u : 1u;
+    nonpositive += (rho <= 0.0 || T <= 0.0) ? 1u : 0u;
+    ++nodes;
   }
-  block_reduce_store<kNumDiag>(acc, partial + (long long)blockIdx.x * kNumDiag);
+
+  __device__ inline void of_differences(double mu, const double (*vn)[3]) {
+    double d[3] = {};
+    d[0] = 0.5 * (vn[0][0] - vn[1][0]);
+    d[1] = 0.5 * (vn[2][1] - vn[3][1]);
+    if (D == 3) d[2] = 0.5 * (vn[4][2] - vn[5][2]);
+    const double wz = 0.5 * (vn[0][1] - vn[1][1]) - 0.5 * (vn[2][0] - vn[3][0]);
+    double wx = 0.0, wy = 0.0;
+    if (D == 3) {
+      wx = 0.5 * (vn[2][2] - vn[3][2]) - 0.5 * (vn[4][1] - vn[5][1]);
+      wy = 0.5 * (vn[4][0] - vn[5][0]) - 0.5 * (vn[0][2] - vn[1][2]);
+    }
+    const double v2 = wx * wx + wy * wy + wz * wz, div = d[0] + d[1] + d[2];
+    div2 += div * div;
+    vort2 += v2;
+    diss += mu * v2;
+#pragma unroll
+    for (int a = 0; a < D; ++a) du2[a] += d[a] * d[a];
+  }
+
+  // in the order of lbm_diag (see diag_from_sums)
+  __device__ inline void store(double (&v)[kNumDiag]) const {
+    const double all[kNumDiag] = {mass,  mom[0], mom[1], mom[2], energy, kinetic, div2,   (u2[0] + u2[1]) + u2[2],
+                                  cs,    rho2,   vort2,  diss,   u2[0],  u2[1],   u2[2],  du2[0],
+                                  du2[1], du2[2], (double)nonfinite, (double)nonpositive, (double)nodes};
+#pragma unroll
+    for (int j = 0; j < kNumDiag; ++j) v[j] = all[j];
+  }
+};
+
+// The diagnostic sums straight from the stored populations.  A work-group
+// takes tiles of BX x BY nodes and marches each over a chunk of planes (z for
+// D3Q27, rows along y for D2Q9): every node's fields are formed once, its
+// velocity goes to LDS for the in-plane differences (a one-node ring around
+// the tile is formed by the first threads), and the march-axis neighbours are
+// the same thread's previous and next planes.  The populations are read once,
+// plus the ring and the two planes next to a chunk; what binds is the latency
+// that two wavefronts per SIMD (180-220 registers: 35 for the sums, 54 or 108
+// for a node's loads) leave open.  256^3: 890 us FP32, 1550 us FP64 (1205 and
+// 1900 us when the fields went through memory and the differences were read
+// back).  Loads in batches of nine: 934 and 1620 us; requested a plane ahead: 880
+// and 1680 us; held to 128 registers it spills; the fields through memory
+// again but with the node sums in that pass: 1040 and 1740 us.
+template <int D, typename S, int BX, int BY>
+__global__ void __launch_bounds__(BX* BY) diag_kernel(const S* __restrict__ pops, double* __restrict__ partial,
+                                                         const StepParams p, const DiagGrid g) {
+  constexpr int LY = (D == 3) ? BY + 2 : 1;
+  constexpr int Q = lat_q(D);
+  constexpr int NHALO = (D == 3) ? 2 * BX + 2 * BY : 2;
+  static_assert(BX * BY >= NHALO, "tile too small for its ring");
+  __shared__ double lu[2][D][LY][BX + 2];
+  const int n0 = p.nx, n1 = (D == 3) ? p.ny : 1, nm = (D == 3) ? p.nz : p.ny;
+  const int bc0 = p.bc[0], bc1 = p.bc[1], bcm = (D == 3) ? p.bc[2] : p.bc[1];
+  const unsigned slot_bytes = (unsigned)(p.sl * (long long)sizeof(S));
+  const long long plane_bytes = p.ms * (long long)sizeof(S);
+  const int t = threadIdx.x, lx = t % BX, ly = t / BX;
+  DiagSums<D> sums;
+  for (int task = blockIdx.x; task < g.tasks; task += gridDim.x) {
+    const int tx = task % g.tiles_x, r = task / g.tiles_x;
+    const int ty = (D == 3) ? r % g.tiles_y : 0, ck = (D == 3) ? r / g.tiles_y : r;
+    const int x0 = tx * BX, y0 = ty * BY, m0 = ck * g.chunk, m1 = min(m0 + g.chunk, nm);
+    // A position beyond the domain stands for the node it maps to by wrap or
+    // clamp; only the first one past each end is anybody's neighbour.
+    auto in_plane = [&](int x, int y) {
+      return inplane_bytes<S>(p, fix_coord(x, n0, bc0) + ((D == 3) ? fix_coord(y, n1, bc1) * n0 : 0));
+    };
+    const int gx = x0 + lx, gy = y0 + ly;
+    const bool active = gx < n0 && gy < n1;
+    const bool formed = gx <= n0 && ((D == 3) ? gy <= n1 : true);
+    const unsigned core = in_plane(gx, gy);
+    int hx = (t == 0) ? -1 : BX, hy = 0;  // the ring node of this thread, within the tile
+    if (D == 3) {
+      if (t < 2 * BX) hx = t % BX, hy = t < BX ? -1 : BY;
+      else hy = (t - 2 * BX) % BY, hx = t < 2 * BX + BY ? -1 : BX;
+    }
+    const bool ring = t < NHALO && x0 + hx <= n0 && ((D == 3) ? y0 + hy <= n1 : true);
+    const unsigned ring_off = in_plane(x0 + hx, y0 + hy);
+    auto load = [&](int m, unsigned off, typename Buf<S>::pair_t* v) {
+      const __amdgpu_buffer_rsrc_t rs = plane_rsrc(pops + (long long)fix_near(m, nm, bcm) * p.ms, plane_bytes);
+#pragma unroll
+      for (int i = 0; i < Q; ++i) v[i] = Buf<S>::load(rs, off, (unsigned)i * slot_bytes);
+    };
+    auto velocity = [&](int m, unsigned off, double* u) {
+      typename Buf<S>::pair_t v[Q];
+      double s0, j[3];
+      load(m, off, v);
+      pair_sums<D>(v, s0, j, nullptr);
+      velocity_of<D>(p, s0, j, u);
+    };
+    auto publish = [&](int buf, int y, int x, const double* u) {
+#pragma unroll
+      for (int a = 0; a < D; ++a) lu[buf][a][(D == 3) ? y + 1 : 0][x + 1] = u[a];
+    };
+    // Fields of plane m: the sums of its nodes, its velocity to LDS and to u,
+    // its viscosity to mu.
+    auto fill = [&](int m, int buf, double* u, double& mu) {
+      if (formed) {
+        double s0, j[3], se, rho, T, rhoE;
+        typename Buf<S>::pair_t v[Q];
+        load(m, core, v);
+        pair_sums<D>(v, s0, j, &se);
+        fields_of<D>(p, s0, j, se, rho, u, T, rhoE);
+        publish(buf, ly, lx, u);
+        if (active) {
+          sums.of_node(p, rho, u, T, rhoE);
+          mu = (p.visc_exp == 0.0) ? p.mu0 : p.mu0 * pow(T * p.inv_Tref, p.visc_exp);
+        }
+      }
+      if (ring) {
+        double uh[3];
+        velocity(m, ring_off, uh);
+        publish(buf, hy, hx, uh);
+      }
+    };
+    double up[3] = {}, uc[3] = {}, un[3] = {};  // velocity at m - 1, m, m + 1
+    double mu = 0, mu_n = 0;
+    if (active) velocity(m0 - 1, core, up);
+    fill(m0, 0, uc, mu);
+    __syncthreads();
+    for (int m = m0; m < m1; ++m) {
+      const int cb = (m - m0) & 1;
+      if (m + 1 < m1) fill(m + 1, cb ^ 1, un, mu_n);
+      else if (active) velocity(m + 1, core, un);
+      if (active) {
+        double vn[6][3] = {};
+        const int yy = (D == 3) ? ly + 1 : 0;
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+          vn[0][a] = lu[cb][a][yy][lx + 2];
+          vn[1][a] = lu[cb][a][yy][lx];
+          if (D == 3) {
+            vn[2][a] = lu[cb][a][(D == 3) ? ly + 2 : 0][lx + 1];
+            vn[3][a] = lu[cb][a][(D == 3) ? ly : 0][lx + 1];
+          }
+          vn[D == 3 ? 4 : 2][a] = un[a];
+          vn[D == 3 ? 5 : 3][a] = up[a];
+        }
+        sums.of_differences(mu, vn);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        up[a] = uc[a];
+        uc[a] = un[a];
+      }
+      mu = mu_n;
+    }
+  }
+  double v[kNumDiag];
+  sums.store(v);
+  block_reduce_store<kNumDiag, BX * BY / 64>(v, partial + blockIdx.x, gridDim.x);
 }
 
-template <int NV>
+// out[j] = the sum of partial[j * nblocks ..]: one work-group per sum, so the
+// partials are read side by side (one work-group for all 21 sums, each
+// thread striding over them, took 11-15 us).
 __global__ void __launch_bounds__(256) final_reduce_kernel(const double* __restrict__ partial, int nblocks,
                                                            double* __restrict__ out) {
-  double acc[NV];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) acc[j] = 0.0;
-  for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-#pragma unroll
-    for (int j = 0; j < NV; ++j) acc[j] += partial[(long long)b * NV + j];
-  }
-  block_reduce_store<NV>(acc, out);
+  double acc[1] = {0.0};
+  for (int b = threadIdx.x; b < nblocks; b += 256) acc[0] += partial[(long long)blockIdx.x * nblocks + b];
+  block_reduce_store<1, 4>(acc, out + blockIdx.x, 1);
 }
 
 // Counts nodes of a candidate initial field with non-finite values or
@@ -918,7 +986,7 @@ __global__ void __launch_bounds__(256) validate_kernel(const double* __restrict_
     for (int a = 0; a < D; ++a) ok = ok && isfinite(u[(long long)a * N + n]);
     acc[0] += ok ? 0.0 : 1.0;
   }
-  block_reduce_store<1>(acc, partial + blockIdx.x);
+  block_reduce_store<1, 4>(acc, partial + blockIdx.x, 1);
 }
 
 __global__ void __launch_bounds__(256) copy_kernel(const float4* __restrict__ src, float4* __restrict__ dst,
@@ -1286,38 +1354,64 @@ __global__ void __launch_bounds__(256) fields_plus_kernel(const double* __restri
   newf[4 * N + n] = k * oldf[4 * N + n] + dT[n];
 }
 
-// coarse node: means of rho, rho u and rho E over its factor^D fine nodes;
-// T from U(T) = E - |u|^2 / 2 with the caloric law of p
-__global__ void __launch_bounds__(256) filter_kernel(const double* __restrict__ fields, long long N, int nx, int ny,
-                                                     int nz, int f, int fz, int D, const StepParams p,
-                                                     double* __restrict__ rho, double* __restrict__ u,
+// Coarse nodes: means of rho, rho u and rho E over factor^D fine nodes,
+// straight from the populations; T from U(T) = E - |u|^2 / 2 with the caloric
+// law of p.  A work-group takes `per` consecutive coarse nodes: a thread sums
+// one fine column x of a coarse node over its f fz rows (consecutive threads,
+// consecutive x), and the f columns are added through LDS.  Bound by reading
+// the populations: 256^3 FP32 by 4, 622 us, 5.8 TB/s (827 + 189 us when the fields went
+// through memory).
+template <int D, typename S>
+__global__ void __launch_bounds__(256) filter_kernel(const S* __restrict__ pops, const StepParams p, int f, int per,
+                                                     int Nc, double* __restrict__ rho, double* __restrict__ u,
                                                      double* __restrict__ T) {
-  const int cx = nx / f, cy = ny / f, cz = nz / fz;
-  const long long Nc = (long long)cx * cy * cz;
-  const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= Nc) return;
-  const int X = (int)(c % cx), Y = (int)((c / cx) % cy), Z = (int)(c / ((long long)cx * cy));
+  __shared__ double red[D + 2][256];
+  const int cx = p.nx / f, cy = p.ny / f, fz = (D == 3) ? f : 1;
+  const int t = threadIdx.x;
+  const int c = blockIdx.x * per + (f <= 256 ? t / f : 0);
   double sr = 0.0, sj[3] = {0.0, 0.0, 0.0}, se = 0.0;
-  for (int k = 0; k < fz; ++k)
-    for (int j = 0; j < f; ++j)
-      for (int i = 0; i < f; ++i) {
-        const long long n = (long long)(X * f + i) + nx * ((long long)(Y * f + j) + (long long)ny * (Z * fz + k));
-        const double r = fields[n];
-        sr += r;
-        for (int a = 0; a < 3; ++a) sj[a] += r * fields[(1 + a) * N + n];
-        se += fields[5 * N + n];
+  if (c < Nc && (f > 256 || t < per * f)) {
+    const int X = c % cx, Y = (c / cx) % cy, Z = c / (cx * cy);
+    for (int k = 0; k < fz; ++k)
+      for (int j = 0; j < f; ++j) {
+        const long long row = (long long)p.nx * ((Y * f + j) + (long long)p.ny * (Z * fz + k)) + (long long)X * f;
+        for (int i = f <= 256 ? t % f : t; i < f; i += f <= 256 ? f : 256) {
+          double s0, jj[3], e;
+          typename Buf<S>::pair_t v[lat_q(D)];
+          load_pairs<D>(pops + pair_offset(p, (int)(row + i)), p, v);
+          pair_sums<D>(v, s0, jj, &e);
+          sr += p.rho0 + s0;
+          se += p.rhoE0 + e;
+#pragma unroll
+          for (int a = 0; a < D; ++a) sj[a] += p.j0[a] + jj[a];
+        }
       }
-  const double inv = 1.0 / sr;
+  }
+  red[0][t] = sr;
+  red[1][t] = se;
+#pragma unroll
+  for (int a = 0; a < D; ++a) red[2 + a][t] = sj[a];
+  __syncthreads();
+  const int o = blockIdx.x * per + t;
+  if (t >= per || o >= Nc) return;
+  const int cols = f <= 256 ? f : 256;
+  double v[D + 2];
+#pragma unroll
+  for (int w = 0; w < D + 2; ++w) {
+    v[w] = 0.0;
+    for (int i = 0; i < cols; ++i) v[w] += red[w][t * cols + i];
+  }
+  const double inv = 1.0 / v[0];
   double u2 = 0.0;
+#pragma unroll
   for (int a = 0; a < D; ++a) {
-    const double ua = sj[a] * inv;
-    u[a * Nc + c] = ua;
+    const double ua = v[2 + a] * inv;
+    u[(long long)a * Nc + o] = ua;
     u2 += ua * ua;
   }
-  const double cnt = (double)f * f * fz;
-  rho[c] = sr / cnt;
-  const double e = se * inv - 0.5 * u2;
-  T[c] = p.caloric ? caloric_step(p.Cv, p.cv1, p.cv2, 0.0, e) : e / p.Cv;
+  rho[o] = v[0] / ((double)f * f * fz);
+  const double e = v[1] * inv - 0.5 * u2;
+  T[o] = p.caloric ? caloric_step(p.Cv, p.cv1, p.cv2, 0.0, e) : e / p.Cv;
 }
 
 hipError_t launch_fields_add(const Ctx& c, void* pops, const double* oldf, const double* newf) {
@@ -1349,38 +1443,74 @@ hipError_t launch_fields_plus(const Ctx& c, const double* oldf, const double* dr
   return hipGetLastError();
 }
 
-hipError_t launch_filter(const Ctx& c, const double* fields, int factor, double* rho, double* u, double* T) {
-  const int fz = c.lattice == 3 ? factor : 1;
-  const long long Nc = (c.n[0] / factor) * (c.n[1] / factor) * (c.n[2] / fz);
-  hipLaunchKernelGGL(filter_kernel, dim3((unsigned)((Nc + 255) / 256)), dim3(256), 0, c.stream, fields, c.N,
-                     (int)c.n[0], (int)c.n[1], (int)c.n[2], factor, fz, c.lattice, c.sp, rho, u, T);
+template <int D, typename S>
+static hipError_t launch_filter_t(const Ctx& c, const void* pops, int f, double* rho, double* u, double* T) {
+  const int64_t Nc = (c.n[0] / f) * (c.n[1] / f) * (D == 3 ? c.n[2] / f : 1);
+  const int per = f <= 256 ? 256 / f : 1;
+  hipLaunchKernelGGL((filter_kernel<D, S>), dim3((unsigned)((Nc + per - 1) / per)), dim3(256), 0, c.stream,
+                     static_cast<const S*>(pops), c.sp, f, per, (int)Nc, rho, u, T);
   return hipGetLastError();
+}
+
+hipError_t launch_filter(const Ctx& c, const void* pops, int factor, double* rho, double* u, double* T) {
+  if (c.lattice == 3)
+    return c.precision == LBM_FP64 ? launch_filter_t<3, double>(c, pops, factor, rho, u, T)
+                                   : launch_filter_t<3, float>(c, pops, factor, rho, u, T);
+  return c.precision == LBM_FP64 ? launch_filter_t<2, double>(c, pops, factor, rho, u, T)
+                                 : launch_filter_t<2, float>(c, pops, factor, rho, u, T);
+}
+
+template <int D, typename S>
+static hipError_t launch_moments_t(const Ctx& c, const void* pops, double* rho, double* u, int nu, double* T) {
+  hipLaunchKernelGGL((fields_kernel<D, S>), dim3((unsigned)((c.N + 255) / 256)), dim3(256), 0, c.stream,
+                     static_cast<const S*>(pops), rho, u, nu, T, (int)c.N, c.sp);
+  return hipGetLastError();
+}
+
+hipError_t launch_moments(const Ctx& c, const void* pops, double* rho, double* u, int nu, double* T) {
+  if (c.lattice == 3)
+    return c.precision == LBM_FP64 ? launch_moments_t<3, double>(c, pops, rho, u, nu, T)
+                                   : launch_moments_t<3, float>(c, pops, rho, u, nu, T);
+  return c.precision == LBM_FP64 ? launch_moments_t<2, double>(c, pops, rho, u, nu, T)
+                                 : launch_moments_t<2, float>(c, pops, rho, u, nu, T);
 }
 
 hipError_t launch_fields(const Ctx& c, const void* pops, double* fields) {
-  const long long N = c.N;
-  const dim3 grid((unsigned)((N + 255) / 256)), block(256);
-  if (c.lattice == 3) {
-    if (c.precision == LBM_FP64)
-      hipLaunchKernelGGL((fields_kernel<3, false, double>), grid, block, 0, c.stream, (const double*)pops, fields, N,
-                         c.sp);
-    else
-      hipLaunchKernelGGL((fields_kernel<3, true, float>), grid, block, 0, c.stream, (const float*)pops, fields, N,
-                         c.sp);
-  } else {
-    if (c.precision == LBM_FP64)
-      hipLaunchKernelGGL((fields_kernel<2, false, double>), grid, block, 0, c.stream, (const double*)pops, fields, N,
-                         c.sp);
-    else
-      hipLaunchKernelGGL((fields_kernel<2, true, float>), grid, block, 0, c.stream, (const float*)pops, fields, N,
-                         c.sp);
-  }
-  return hipGetLastError();
+  return launch_moments(c, pops, fields, fields + c.N, 3, fields + 4 * c.N);
 }
 
-int diag_blocks(const Ctx& c) {
+int validate_blocks(const Ctx& c) {
   const long long want = (c.N + 255) / 256;
   return (int)(want < kMaxDiagBlocks ? want : kMaxDiagBlocks);
+}
+
+// Work-groups and march chunks of the diagnostics: 64 x 8 tiles (a smaller
+// ring to read again: 890 us at 256^3 FP32 against 1030 for 64 x 4) as long as
+// they leave every compute unit a work-group, else 64 x 4; chunks as long as
+// that allows, as each reads two more planes, but of at least 4.
+DiagGrid diag_grid(const Ctx& c) {
+  DiagGrid g{};
+  const int64_t nm = c.lattice == 3 ? c.n[2] : c.n[1];
+  auto shape = [&](int bx, int by, int64_t target) {
+    g.by = by;
+    g.tiles_x = (int)((c.n[0] + bx - 1) / bx);
+    g.tiles_y = c.lattice == 3 ? (int)((c.n[1] + by - 1) / by) : 1;
+    const int64_t tiles = (int64_t)g.tiles_x * g.tiles_y;
+    const int64_t chunks = tiles < target ? target / tiles : 1;
+    int64_t chunk = (nm + chunks - 1) / chunks;
+    if (chunk < 4) chunk = nm < 4 ? nm : 4;
+    g.chunk = (int)chunk;
+    const int64_t tasks = tiles * ((nm + chunk - 1) / chunk);
+    g.tasks = (int)tasks;
+    g.blocks = (int)(tasks < kMaxDiagBlocks ? tasks : kMaxDiagBlocks);
+  };
+  if (c.lattice == 2) {
+    shape(256, 1, 1024);
+    return g;
+  }
+  shape(64, 8, 256);
+  if (g.tasks < 256) shape(64, 4, 1024);
+  return g;
 }
 
 // Device memory of the allocation-free diagnostics (lbm_diagnostics_noalloc):
@@ -1397,36 +1527,29 @@ hipError_t scratch_address(double** out) {
   return e;
 }
 
-hipError_t launch_diag_direct(const Ctx& c, const void* pops, double* partial, int nblocks, double* out) {
+template <int D, typename S, int BX, int BY>
+static void launch_diag_t(const Ctx& c, const void* pops, double* partial, const DiagGrid& g) {
+  hipLaunchKernelGGL((diag_kernel<D, S, BX, BY>), dim3(g.blocks), dim3(BX * BY), 0, c.stream,
+                     static_cast<const S*>(pops), partial, c.sp, g);
+}
+
+hipError_t launch_diag(const Ctx& c, const void* pops, double* partial, const DiagGrid& g, double* out) {
   if (c.lattice == 3) {
-    if (c.precision == LBM_FP64)
-      hipLaunchKernelGGL((diag_direct_kernel<3, double>), dim3(nblocks), dim3(256), 0, c.stream,
-                         static_cast<const double*>(pops), partial, (long long)c.N, c.sp);
-    else
-      hipLaunchKernelGGL((diag_direct_kernel<3, float>), dim3(nblocks), dim3(256), 0, c.stream,
-                         static_cast<const float*>(pops), partial, (long long)c.N, c.sp);
+    if (c.precision == LBM_FP64) {
+      if (g.by == 8) launch_diag_t<3, double, 64, 8>(c, pops, partial, g);
+      else launch_diag_t<3, double, 64, 4>(c, pops, partial, g);
+    } else {
+      if (g.by == 8) launch_diag_t<3, float, 64, 8>(c, pops, partial, g);
+      else launch_diag_t<3, float, 64, 4>(c, pops, partial, g);
+    }
+  } else if (c.precision == LBM_FP64) {
+    launch_diag_t<2, double, 256, 1>(c, pops, partial, g);
   } else {
-    if (c.precision == LBM_FP64)
-      hipLaunchKernelGGL((diag_direct_kernel<2, double>), dim3(nblocks), dim3(256), 0, c.stream,
-                         static_cast<const double*>(pops), partial, (long long)c.N, c.sp);
-    else
-      hipLaunchKernelGGL((diag_direct_kernel<2, float>), dim3(nblocks), dim3(256), 0, c.stream,
-                         static_cast<const float*>(pops), partial, (long long)c.N, c.sp);
+    launch_diag_t<2, float, 256, 1>(c, pops, partial, g);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((final_reduce_kernel<kNumDiag>), dim3(1), dim3(256), 0, c.stream, partial, nblocks, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_diag(const Ctx& c, const double* fields, double* partial, int nblocks, double* out) {
-  if (c.lattice == 3)
-    hipLaunchKernelGGL((diag_kernel<3>), dim3(nblocks), dim3(256), 0, c.stream, fields, partial, (long long)c.N, c.sp);
-  else
-    hipLaunchKernelGGL((diag_kernel<2>), dim3(nblocks), dim3(256), 0, c.stream, fields, partial, (long long)c.N, c.sp);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((final_reduce_kernel<kNumDiag>), dim3(1), dim3(256), 0, c.stream, partial, nblocks, out);
+  hipLaunchKernelGGL(final_reduce_kernel, dim3(kNumDiag), dim3(256), 0, c.stream, partial, g.blocks, out);
   return hipGetLastError();
 }
 
@@ -1440,7 +1563,7 @@ hipError_t launch_validate(const Ctx& c, const double* rho, const double* u, con
                        (long long)c.N);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((final_reduce_kernel<1>), dim3(1), dim3(256), 0, c.stream, partial, nblocks, out);
+  hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(256), 0, c.stream, partial, nblocks, out);
   return hipGetLastError();
 }
 

@@ -1,0 +1,107 @@
+"""The moments, diagnostics and box filter, which read the populations
+directly: every lattice, storage and boundary at the edges of their tiles and
+work-groups, against the oracle's populations and plain numpy sums of its
+moments."""
+import numpy as np
+import pytest
+
+from paper_2102_09512_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# 64 x 8 and 64 x 4 (D3Q27) and 256 x 1 (D2Q9) tiles: one node, below, at and
+# just past the tile edges, several chunks, several work-group shapes
+DIMS = [(2, (1, 1)), (2, (255, 3)), (2, (257, 33)), (2, (64, 700)), (3, (1, 1, 1)), (3, (64, 8, 5)), (3, (65, 9, 4)),
+        (3, (63, 7, 70)), (3, (129, 33, 40)), (3, (200, 130, 37))]
+
+
+def _sums(D, rho, u, T, clamp, mu, visc_exp, T_ref, cv):
+    def d(q, a):  # central difference along axis a (x is the last)
+        n = q.shape[2 - a]
+        k = np.arange(n)
+        hi, lo = ((np.minimum(k + 1, n - 1), np.maximum(k - 1, 0)) if clamp[a] else ((k + 1) % n, (k - 1) % n))
+        return 0.5 * (q.take(hi, 2 - a) - q.take(lo, 2 - a))
+
+    g = [[d(u[c], a) for a in range(D)] for c in range(D)]
+    w = [g[1][0] - g[0][1]] + ([g[2][1] - g[1][2], g[0][2] - g[2][0]] if D == 3 else [])
+    w2, uu = sum(x * x for x in w), (u * u).sum(0)
+    three = lambda v: v + [0.0] * (3 - D)
+    return dict(mass=rho.sum(), momentum=three([(rho * u[a]).sum() for a in range(D)]),
+                energy=(rho * (cv * T + 0.5 * uu)).sum(), kinetic_energy=(0.5 * rho * uu).sum(),
+                dilatation_sq_sum=(sum(g[a][a] for a in range(D)) ** 2).sum(), u2_sum=uu.sum(),
+                cs_sum=np.sqrt(1.4 * T).sum(), rho2_sum=(rho * rho).sum(), vorticity_sq_sum=w2.sum(),
+                dissipation_sum=(mu * (T / T_ref) ** visc_exp * w2).sum(),
+                u_axis_sq_sum=three([(u[a] ** 2).sum() for a in range(D)]),
+                du_axis_sq_sum=three([(g[a][a] ** 2).sum() for a in range(D)]), nodes=rho.size)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("bc", [(0, 0, 0), (1, 0, 1), (0, 1, 0)])
+@pytest.mark.parametrize("lattice,dims", DIMS)
+def test_moments_and_diagnostics(lattice, dims, bc, precision):
+    import torch
+
+    from paper_2102_09512_amd import lbm
+
+    print("[gpu case] moments and diagnostics", lattice, dims, bc, precision, flush=True)
+    D = lattice
+    rho, u, T = I.smooth_random(D, dims, seed=5)
+    u = u + 0.03
+    h = lbm.lbm_create(D, dims, 1.4, 0.7, 0.02, precision=precision, bc=bc, visc_exponent=0.76, T_ref=0.15)
+    try:
+        lbm.lbm_init_fields(h, rho, u, T)
+        dev = [torch.full(a.shape, np.nan, dtype=torch.float64, device="cuda") for a in (rho, u, T)]
+        lbm.lbm_moments(h, *dev)
+        host = [np.full(a.shape, np.nan) for a in (rho, u, T)]
+        lbm.lbm_moments(h, *host)
+        only = torch.full(T.shape, np.nan, dtype=torch.float64, device="cuda")
+        lbm.lbm_moments(h, T=only)
+        for a, b, ref in zip(dev, host, (rho, u, T)):
+            assert np.array_equal(a.cpu().numpy(), b)
+            # FP64: sums of 27 values; FP32: each stored deviation is rounded once (2^-24 of at most ~0.1)
+            assert np.abs(b - ref).max() <= (1e-13 if precision == 0 else 27 * 2.0 ** -24)
+        assert np.array_equal(only.cpu().numpy(), host[2])
+        got, direct = lbm.lbm_diagnostics(h), lbm.lbm_diagnostics_noalloc(h)
+        assert got == direct == lbm.lbm_diagnostics(h)  # one kernel, a fixed order
+        ref = _sums(D, *host, [b == 1 for b in bc], 0.02, 0.76, 0.15, 2.5)
+        for k, v in ref.items():
+            # a few thousand roundings of relative size 2^-53, on sums whose terms have one sign or a mean
+            # velocity well above their scatter; the differences lose |u| / |du| <= 1e3 more
+            scale = np.abs(np.asarray(v)) + 1e-10 * rho.size
+            assert np.all(np.abs(np.asarray(got[k]) - np.asarray(v)) <= 1e-11 * scale), (k, got[k], v)
+        assert got["nonfinite"] == got["nonpositive"] == 0
+    finally:
+        lbm.lbm_destroy(h)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("lattice,dims,factor", [(2, (6, 4), 1), (2, (6, 4), 2), (2, (770, 6), 2), (2, (600, 300), 300),
+                                                 (3, (8, 4, 12), 4), (3, (96, 12, 9), 3), (3, (15, 35, 20), 5),
+                                                 (3, (256, 16, 16), 8)])
+def test_filter(lattice, dims, factor, precision):
+    import torch
+
+    from paper_2102_09512_amd import lbm
+
+    print("[gpu case] filter", lattice, dims, factor, precision, flush=True)
+    D, f = lattice, factor
+    h = lbm.lbm_create(D, dims, 1.4, 0.7, 0.02, precision=precision, T_ref=0.15)
+    try:
+        lbm.lbm_init_fields(h, *I.smooth_random(D, dims, seed=9))
+        rho, u, T = [np.empty(a.shape) for a in I.smooth_random(D, dims, seed=9)]
+        lbm.lbm_moments(h, rho, u, T)
+        nx, ny, nz = [n // f for n in dims[:2]] + [dims[2] // f if D == 3 else 1]
+        fz = f if D == 3 else 1
+        mean = lambda a: a.reshape(nz, fz, ny, f, nx, f).mean((1, 3, 5))
+        r = mean(rho)
+        v = np.stack([mean(rho * u[a]) / r for a in range(D)])
+        t = 0.4 * (mean(rho * (2.5 * T + 0.5 * (u * u).sum(0))) / r - 0.5 * (v * v).sum(0))
+        out = [np.empty_like(r), np.empty_like(v), np.empty_like(t)]
+        lbm.lbm_filter_moments(h, f, *out)
+        dev = [torch.empty(a.shape, dtype=torch.float64, device="cuda") for a in out]
+        lbm.lbm_filter_moments(h, f, *dev)
+        for a, b, ref in zip(out, dev, (r, v, t)):
+            assert np.array_equal(a, b.cpu().numpy())
+            assert np.abs(a - ref).max() <= 1e-13  # means of values up to ~1, in two summation orders
+    finally:
+        lbm.lbm_destroy(h)
