@@ -685,6 +685,11 @@ int batch_layout(Batch* b) {
     const lbm::Ctx* c = b->boxes[i];
     lbm::Tile t = b->tile;
     const int64_t nm = c->lattice == 3 ? c->n[2] : c->n[1];
+    if (t.chunk <= 0 && b->auto_tile && c->lattice == 3) {
+      // the chunk that the box has on its own, where it has this shape there
+      const lbm::Tile own = lbm::default_tile(c->lattice, c->precision, c->n);
+      if (own.bx == t.bx && own.by == t.by) t.chunk = own.chunk;
+    }
     if (t.chunk <= 0) t.chunk = lbm::default_chunk(c->lattice, c->n, t.bx, t.by);
     if (t.chunk > nm) t.chunk = (int)nm;
     lbm::BoxEntry& e = b->host[i];
@@ -834,6 +839,7 @@ int lbm_batch_set_tile(lbm_batch b, const int tile[3]) {
   int rc = batch_select_device(b);
   if (rc != LBM_OK) return rc;
   b->tile = t;
+  b->auto_tile = false;
   return batch_layout(b);
 }
 
@@ -874,6 +880,7 @@ int lbm_batch_tune(lbm_batch b, int reps, double* best_ms) {
   }
   // Every timed launch reads each box's current buffer and writes the other
   // one (flip 0, no toggle), so the states are left as they were.
+  const bool auto_tile = b->auto_tile;
   lbm::Tile best = b->tile;
   bool best_persistent = b->persistent;
   float best_t = -1.0f;
@@ -904,6 +911,7 @@ int lbm_batch_tune(lbm_batch b, int reps, double* best_ms) {
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
   b->tile = best;
+  b->auto_tile = auto_tile && best.chunk == 0;
   b->persistent = best_persistent;
   const int rc2 = batch_layout(b);
   if (rc != LBM_OK) return rc;

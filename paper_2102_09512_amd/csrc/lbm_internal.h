@@ -112,6 +112,7 @@ struct Batch {
   std::vector<int> cur_dev;        // cur of each box as the device table holds it
   int total_blocks = 0;
   Tile tile{};                     // bx, by shared by all boxes; chunk 0 = per-box default
+  bool auto_tile = true;           // the default tile (none set or tuned)
   bool persistent = false;         // fixed grid looping over the tiles instead of one work-group per tile
   hipStream_t user_stream = nullptr;
   hipStream_t own_stream = nullptr;  // graph replays run here

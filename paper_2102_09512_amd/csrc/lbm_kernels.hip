@@ -37,6 +37,8 @@
 // processes one contiguous range of tiles (neighbouring tiles share an L2).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "lbm_internal.h"
 #include "lbm_node.h"
 
@@ -1098,24 +1100,91 @@ int default_chunk(int D, const int64_t n[3], int bx, int by) {
   return (int)(chunk < n[1] ? chunk : n[1]);
 }
 
+// A finer model of a launch, for the shapes whose results do not depend on the
+// march chunk (FP64, and 64 x 8 in FP32: one plane in flight, one copy of the
+// plane's arithmetic).  A work-group marches c planes of one tile column and
+// pays p1 planes for its start (launch, the planes next to the chunk, its first
+// loads); one that follows another on its compute unit pays less, p2.  The
+// device holds cap2 work-groups of the shape at a time; w2 is what a plane
+// takes them, and w1 what it takes up to cap1 of them, which share no SIMD.  A
+// round that leaves some compute units idle runs a little faster (`idle`;
+// D3Q27, where memory binds).  Fitted to sweeps of shape and chunk: the chosen
+// one is within 6% of the fastest of the sweep at 20x25x40, 64^3, 80^3, 96^3,
+// 100^3, 128^3, 160^3, 190x131x110, 192^3, 256^3, 256x256x32 and, in D2Q9, 800x4,
+// 300^2, 600x500, 1000x333, 200x1600, 1024^2, 2048^2.  Against the powers of two
+// of march_cost (us per step, same kernel): FP64 20x25x40 64x4/4 31.4, 32x8/1
+// 14.6; 100^3 64x4/32 285, 64x4/20 210; 190x131x110 64x4/16 600, 64x4/55 555;
+// 800x4 128x1/4 13.7, 128x1/1 7.3; 300^2 128x1/4 15.1, 128x1/1 10.7; FP32
+// 190x131x110 64x8/32 346, 64x8/22 296.
+struct ShapeModel {
+  int bx, by, cap1, cap2;
+  double w1, w2, p1, p2, idle;
+};
+
+static double launch_time(const ShapeModel& s, int64_t blocks, double c) {
+  auto filled = [&](int64_t b) { return 1.0 - s.idle * (1.0 - std::max(0.75, (double)b / s.cap2)); };
+  if (blocks <= s.cap2) return (blocks <= s.cap1 ? s.w1 : s.w2) * (c + s.p1) * filled(blocks);
+  const double rounds = (double)blocks / s.cap2;
+  // over many rounds a compute unit takes the next work-group as it gets free
+  if (rounds > 3.0) return s.w2 * ((c + s.p1) + (rounds - 1.0) * (c + s.p2));
+  const int64_t whole = blocks / s.cap2, rest = blocks % s.cap2;
+  double t = s.w2 * ((c + s.p1) + (double)(whole - 1) * (c + s.p2));
+  if (rest) t += (rest <= s.cap1 ? s.w1 : s.w2) * (c + s.p2) * filled(rest);
+  return t;
+}
+
+// One work-group per compute unit.
+static const ShapeModel kShape64x8{64, 8, 256, 256, 1.5, 1.5, 7.0, 6.0, 0.2};
+static const ShapeModel kShapes3F64[] = {{64, 4, 256, 256, 1.0, 1.0, 15.0, 13.0, 0.2},
+                                         {32, 8, 256, 256, 1.02, 1.02, 15.0, 13.0, 0.2}};
+// Two wavefronts per SIMD; two work-groups of a compute unit share SIMDs.
+static const ShapeModel kShape2F64[] = {{128, 1, 256, 1024, 1.03, 1.45, 3.0, 1.5, 0.0},
+                                        {256, 1, 256, 512, 1.06, 1.43, 3.0, 1.5, 0.0}};
+
+// The model's best of the shapes and of the chunks of at most `longest` planes
+// that split the march axis evenly (longer ones gain nothing more).
+static Tile best_tile(const ShapeModel* shapes, int count, const int64_t n[3], int64_t nm, int64_t longest) {
+  Tile best{0, 0, 1};
+  double best_time = 0.0;
+  for (int k = 0; k < count; ++k) {
+    const ShapeModel& s = shapes[k];
+    const int64_t tiles = ((n[0] + s.bx - 1) / s.bx) * (s.by > 1 ? (n[1] + s.by - 1) / s.by : 1);
+    for (int64_t c = 1; c <= longest && c <= nm; ++c) {
+      const int64_t chunks = (nm + c - 1) / c;
+      if ((nm + chunks - 1) / chunks != c) continue;
+      const double t = launch_time(s, tiles * chunks, (double)c);
+      if (!best.bx || t < best_time) {
+        best_time = t;
+        best = Tile{s.bx, s.by, (int)c};
+      }
+    }
+  }
+  return best;
+}
+
 // Default launch shape and march chunk (32 x 16 tiles, the 512-thread shape
 // with the smallest halo ring, measured 10% slower than 64 x 8 at 256^3 FP32
-// and are not compiled).  D3Q27: the compiled shape with the
-// lowest march_cost at its best chunk — 64 x 4, 32 x 8 and, for FP32
-// storage, 64 x 8 (the only 512-thread shape that fits 256 registers
-// without spilling); the caloric variant is compiled for 64 x 4 only.  On
-// one MI355X this picks 64 x 4 with 4-plane chunks at 64^3 (2.1x the
-// throughput of 16-plane chunks), 32 x 8 / 16 at 96^3, 64 x 8 / 16 at 128^3
-// (3.6% faster than 64 x 4 / 32), 64 x 8 / 64 at 192^3, 64 x 8 / 128 at
-// 256^3 (9% faster than 64 x 4 / 256 there) and 64 x 8 / 16 for a
-// 256 x 256 x 32 slab (8% faster than 64 x 4 / 32).  D2Q9: rows of 128, or of 256 from 1024 nodes per row
-// (FP32: 9% faster at 4096^2, even at 1024^2 and 2048^2; FP64 at 1024^2: 4%
-// faster).
+// and are not compiled).  The caloric variant is compiled for one shape of each
+// lattice.
+// D3Q27 FP32: the shape with the lowest march_cost at its best chunk, and for
+// 64 x 8 (the only 512-thread shape that fits 256 registers without spilling)
+// the chunk of the finer model.  The 256-thread FP32 shapes keep two planes in
+// flight through a plane loop unrolled three times; the compiler fuses products
+// and sums a little differently in each copy, so there the rounding of a node
+// follows the chunk, and a different chunk moves the results of long runs, and
+// of runs with the bf16 corrector, by more than rounding (5e-5 of the deviations
+// after four corrections).  On one MI355X this picks 64 x 4 / 4 at 64^3, 64 x 8 /
+// 16 at 128^3 and for a 256 x 256 x 32 slab, 64 x 8 / 128 at 256^3 (9% faster
+// than 64 x 4 / 256 there).
+// D2Q9: rows of 128, or of 256 from 1024 nodes per row (FP32: 9% faster at
+// 4096^2, even at 1024^2 and 2048^2; FP64 at 1024^2: 4% faster).  FP32 keeps two
+// rows in flight, so its chunks stay as they are too.
 Tile default_tile(int D, int precision, const int64_t n[3], bool caloric) {
   if (D == 3) {
+    if (precision == LBM_FP64) return best_tile(kShapes3F64, caloric ? 1 : 2, n, n[2], 256);
     struct Shape { int bx, by; double w; };
     const Shape shapes[3] = {{64, 4, 1.0}, {32, 8, 1.02}, {64, 8, 1.82}};
-    const int nshapes = caloric ? 1 : (precision == LBM_FP32_DEV ? 3 : 2);
+    const int nshapes = caloric ? 1 : 3;
     Tile best{64, 4, 1};
     double best_cost = -1.0;
     for (int s = 0; s < nshapes; ++s) {
@@ -1126,9 +1195,11 @@ Tile default_tile(int D, int precision, const int64_t n[3], bool caloric) {
         best = Tile{shapes[s].bx, shapes[s].by, (int)c};
       }
     }
-    return best;
+    return best.by == 8 && best.bx == 64 ? best_tile(&kShape64x8, 1, n, n[2], 256) : best;
   }
-  const int bx = (!caloric && n[0] >= 1024) ? 256 : 128;
+  const bool wide = !caloric && n[0] >= 1024;
+  if (precision == LBM_FP64) return best_tile(&kShape2F64[wide ? 1 : 0], 1, n, n[1], 32);
+  const int bx = wide ? 256 : 128;
   return Tile{bx, 1, default_chunk(D, n, bx, 1)};
 }
 
