@@ -219,24 +219,20 @@ void diag_from_sums(Ctx* c, const double* v, lbm_diag* out) {
 
 }  // namespace
 
-// For the corrector (lbm_nn.hip): the moments of the stored state into
-// c->fields (rho, u_x, u_y, u_z, T, rho E planes) on the handle's stream, and
-// increments applied by re-equilibration without validation or host
-// synchronisation (the caller bounds them).
-int lbm::fields_current(lbm::Ctx* base) {
+// For the corrector (lbm_nn.hip): the state's input planes, and corrections
+// applied by re-equilibration without validation or host synchronisation (the
+// caller bounds them).
+int lbm::corrector_planes(lbm::Ctx* base, float* x) {
   lbm_ctx* c = static_cast<lbm_ctx*>(base);  // every handle is an lbm_ctx
   if (!c->initialised) return fail(LBM_ESTATE, "corrector: no state (lbm_init_fields)");
-  int rc = ::select_device(c);
+  const int rc = ::select_device(c);
   if (rc) return rc;
-  if ((rc = ::ensure_fields(c))) return rc;
-  HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], c->fields), "moments kernel");
+  HIP_OR_FAIL(lbm::launch_planes(*c, c->buf[c->cur], x), "moments kernel");
   return LBM_OK;
 }
 
-int lbm::fields_increment_async(Ctx* c, const double* drho, const double* du, const double* dT) {
-  if (!c->work) HIP_OR_FAIL(hipMalloc(&c->work, sizeof(double) * 10 * (size_t)c->N), "hipMalloc(work)");
-  HIP_OR_FAIL(lbm::launch_fields_plus(*c, c->fields, drho, du, dT, c->work, true), "increment kernel");
-  HIP_OR_FAIL(lbm::launch_fields_add(*c, c->buf[c->cur], c->fields, c->work), "re-equilibration kernel");
+int lbm::corrector_apply(Ctx* c, const float* y, const float* sd, int channels, int offset, float limit) {
+  HIP_OR_FAIL(lbm::launch_correct(*c, c->buf[c->cur], y, sd, channels, offset, limit), "re-equilibration kernel");
   return LBM_OK;
 }
 
@@ -594,7 +590,7 @@ static int fields_update(lbm_handle h, const double* drho, const double* du, con
   if (!c->initialised) return fail(LBM_ESTATE, std::string(name) + ": no state (lbm_init_fields)");
   int rc = select_device(c);
   if (rc) return rc;
-  if ((rc = ensure_fields(c)) || (rc = ensure_partials(c))) return rc;
+  if ((rc = ensure_partials(c))) return rc;
   const int64_t N = c->N;
   const int D = c->lattice;
   if (!c->work) HIP_OR_FAIL(hipMalloc(&c->work, sizeof(double) * 10 * (size_t)N), "hipMalloc(work)");
@@ -608,16 +604,14 @@ static int fields_update(lbm_handle h, const double* drho, const double* du, con
     du = st + N;
     dT = st + 4 * N;
   }
-  HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], c->fields), "moments kernel");
-  HIP_OR_FAIL(lbm::launch_fields_plus(*c, c->fields, drho, du, dT, newf, keep), "increment kernel");
-  HIP_OR_FAIL(lbm::launch_validate(*c, newf, newf + N, newf + 4 * N, c->partial, lbm::validate_blocks(*c),
-                                   c->diag_dev),
-              "validate");
+  HIP_OR_FAIL(lbm::launch_fields_new(*c, c->buf[c->cur], drho, du, dT, keep, newf, c->partial,
+                                     lbm::validate_blocks(*c), c->diag_dev),
+              "new fields");
   double bad = 0.0;
   HIP_OR_FAIL(hipMemcpyAsync(&bad, c->diag_dev, sizeof(double), hipMemcpyDeviceToHost, c->stream), "copy count");
   HIP_OR_FAIL(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
   if (bad != 0.0) return fail(LBM_EINVAL, std::string(name) + ": non-finite value or rho <= 0 or T <= 0 in the new fields");
-  HIP_OR_FAIL(lbm::launch_fields_add(*c, c->buf[c->cur], c->fields, newf), "re-equilibration kernel");
+  HIP_OR_FAIL(lbm::launch_fields_add(*c, c->buf[c->cur], newf), "re-equilibration kernel");
   return LBM_OK;
 }
 

@@ -73,7 +73,7 @@ struct Ctx {
   void* buf[2] = {nullptr, nullptr}; // population buffers (2Q x ps elements each)
   int cur = 0;                       // buffer holding the current state
   double* fields = nullptr;          // 5 x N doubles, on first use: rho, ux, uy, uz, T
-  double* work = nullptr;            // 10 x N doubles, on first use: new fields and staged increments
+  double* work = nullptr;            // 10 x N doubles, on first use: new fields and staged host arrays
   double* partial = nullptr;         // per-block partial sums
   double* diag_dev = nullptr;        // final sums
   bool initialised = false;
@@ -146,14 +146,21 @@ hipError_t launch_pack(const Ctx& c, const void* pops, void* state);
 hipError_t launch_unpack(const Ctx& c, const void* state, void* pops);
 // Records msg as the calling thread's last error (lbm_last_error); returns code.
 int set_error(int code, const std::string& msg);
-hipError_t launch_fields_add(const Ctx& c, void* pops, const double* oldf, const double* newf);
-hipError_t launch_fields_plus(const Ctx& c, const double* oldf, const double* drho, const double* du, const double* dT,
-                              double* newf, bool keep);
+// Re-equilibration: to the fields in the planes rho, u_x, u_y, u_z, T of newf,
+// or by the corrector's normalised outputs y (see Corrected).
+hipError_t launch_fields_add(const Ctx& c, void* pops, const double* newf);
+hipError_t launch_correct(const Ctx& c, void* pops, const float* y, const float* sd, int channels, int offset,
+                          float limit);
+// The new fields keep * old + d into newf, and the number of bad nodes into out.
+hipError_t launch_fields_new(const Ctx& c, const void* pops, const double* drho, const double* du, const double* dT,
+                             bool keep, double* newf, double* partial, int nblocks, double* out);
+// rho, u, T as FP32 planes x[D + 2][N].
+hipError_t launch_planes(const Ctx& c, const void* pops, float* x);
 hipError_t launch_filter(const Ctx& c, const void* pops, int factor, double* rho, double* u, double* T);
-// Corrector support (host, lbm_api.hip): moments into c->fields; increments
-// applied by re-equilibration, asynchronously and without validation.
-int fields_current(Ctx* c);
-int fields_increment_async(Ctx* c, const double* drho, const double* du, const double* dT);
+// Corrector support (host, lbm_api.hip): the state's input planes, and a
+// correction applied without validation, both on the handle's stream.
+int corrector_planes(Ctx* c, float* x);
+int corrector_apply(Ctx* c, const float* y, const float* sd, int channels, int offset, float limit);
 hipError_t launch_batch_step(const Batch& b, hipStream_t s, int flip);
 hipError_t launch_toggle(const Batch& b, hipStream_t s);
 // Default launch tile for a lattice/precision, the default march chunk for a

@@ -1373,56 +1373,179 @@ hipError_t launch_init(const Ctx& c, const double* rho, const double* u, const d
 // Field increments by re-equilibration, and the conservative box filter
 // ---------------------------------------------------------------------------
 
+// f^eq - w and g^eq - w of one node in FP64, a row of three c_x at a time (see
+// EqBuilder).  Without an anomaly the factors of f are the a-factors of g, so
+// half of EqBuilder's state is enough.
+template <int D, bool DEV>
+struct NodeEq {
+  AxisG<double> Y, Z;
+  double g1[3], g2[3], eps, deps;
+
+  __device__ inline NodeEq(const NodeConsts& k, double rho, const double* u, double T) {
+    const double drho = rho - k.rho0, dT = T - k.T0;
+    auto axis = [&](int a) { return axis_g<double, DEV>(u[a], u[a] - k.u0[a], k.u0[a], T, dT, k.T0); };
+    const AxisG<double> X = axis(0);
+    Y = axis(1);
+    if (D == 3) Z = axis(2);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      g1[c] = drho * X.a[c] + (DEV ? k.rho0 * X.da[c] : 0.0);
+      g2[c] = drho * X.b[c] + (DEV ? k.rho0 * X.db[c] : 0.0);
+    }
+    deps = k.caloric ? caloric_du<double>(k.Cv, k.cv1, k.cv2, k.T0, dT) : k.Cv * dT;
+    eps = k.caloric ? k.U0 + deps : k.Cv * T;
+  }
+
+  // What the populations of row p (c_y, c_z) need besides g1 and g2:
+  // f = g1 A + rho0 psi0_x dA, g = g1 V1 + g2 A + rho0 (psi0_x V2 + b0_x dA).
+  struct Row {
+    double A, V1, dA, V2;
+  };
+  __device__ inline Row row(const NodeConsts& k, int p) const {
+    const int jy = p % 3, jz = p / 3;
+    const double a0 = k.psi0[1][jy], b0 = k.b0[1][jy];
+    Row r;
+    r.A = Y.a[jy];
+    r.dA = Y.da[jy];
+    double B = Y.b[jy], dB = Y.db[jy];
+    if (D == 3) {
+      r.A = Y.a[jy] * Z.a[jz];
+      B = Y.b[jy] * Z.a[jz] + Y.a[jy] * Z.b[jz];
+      r.dA = Y.da[jy] * Z.a[jz] + a0 * Z.da[jz];
+      dB = Y.db[jy] * Z.a[jz] + b0 * Z.da[jz] + Y.da[jy] * Z.b[jz] + a0 * Z.db[jz];
+    }
+    r.V1 = eps * r.A + B;
+    r.V2 = deps * r.A + (k.caloric ? k.U0 : k.Cv * k.T0) * r.dA + dB;
+    return r;
+  }
+};
+
+// New fields of a node: the planes rho, u_x, u_y, u_z, T of F ...
+struct NewFields {
+  const double* F;
+  long long N;
+  __device__ inline void operator()(long long n, double& rho, double* u, double& T) const {
+    rho = F[n];
+    for (int a = 0; a < 3; ++a) u[a] = F[(1 + a) * N + n];
+    T = F[4 * N + n];
+  }
+};
+
+// ... or the old ones and the normalised corrections y[c][n], output c for
+// field off + c (0 rho, 1..D u, D + 1 T); with limit > 0 a correction is
+// clipped to [-limit, limit] first.
+template <int D>
+struct Corrected {
+  const float *y, *sd;
+  int C, off;
+  float limit;
+  long long N;
+  __device__ inline void operator()(long long n, double& rho, double* u, double& T) const {
+#pragma unroll
+    for (int f = 0; f < D + 2; ++f) {
+      const int c = f - off;
+      double inc = 0.0;
+      if (c >= 0 && c < C) {
+        float v = y[(long long)c * N + n];
+        if (limit > 0.f) v = fminf(fmaxf(v, -limit), limit);
+        inc = (double)v * sd[c];
+      }
+      if (f == 0) rho += inc;
+      else if (f <= D) u[f - 1] += inc;
+      else T += inc;
+    }
+  }
+};
+
 // f_i += f^eq_i(new) - f^eq_i(old), g likewise (equilibria evaluated in FP64
-// for either storage).  oldf, newf: rho, ux, uy, uz, T planes (N each).
-template <int D, bool DEV, typename S>
-__global__ void __launch_bounds__(256) fields_add_kernel(S* __restrict__ pops, const double* __restrict__ oldf,
-                                                         const double* __restrict__ newf, long long N,
+// for either storage), the old fields those of the populations themselves.
+// The populations are read and written once; with two equilibria a node in
+// 2 x 60 registers, FP64 arithmetic and the latency of a few wavefronts bind
+// at the corrector's 64^3: 29.6 us (45.2 us with the old fields from memory and
+// both equilibria whole in registers, and 28 us for the kernels around it).
+template <int D, bool DEV, typename S, typename New>
+__global__ void __launch_bounds__(256, 2) fields_add_kernel(S* __restrict__ pops, const New fresh, int N,
                                                          const StepParams p) {
+  using pair_t = typename Buf<S>::pair_t;
   constexpr int Q = lat_q(D);
-  const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
   const NodeConsts k = node_consts(p);
-  double fo[Q], go[Q], fn[Q], gn[Q];
-  const double d0[3] = {0.0, 0.0, 0.0};
+  S* at = pops + pair_offset(p, n);
+  pair_t v[Q];
+  load_pairs<D>(at, p, v);
+  double s0, j[3], se, rho, u[3], T, rhoE;
+  pair_sums<D>(v, s0, j, &se);
+  fields_of<D>(p, s0, j, se, rho, u, T, rhoE);
+  const NodeEq<D, DEV> before(k, rho, u, T);
+  fresh(n, rho, u, T);
+  const NodeEq<D, DEV> after(k, rho, u, T);
 #pragma unroll
-  for (int w = 0; w < 2; ++w) {
-    const double* F = w ? newf : oldf;
-    NodeMoments<double> m;
-    m.rho = F[n];
-    m.drho = F[n] - p.rho0;
-    m.T = F[4 * N + n];
-    m.dT = F[4 * N + n] - p.T0;
-    for (int a = 0; a < 3; ++a) {
-      const double ua = a < D ? F[(1 + a) * N + n] : 0.0;
-      m.u[a] = ua;
-      m.du[a] = ua - p.u0[a];
+  for (int r = 0; r < Q / 3; ++r) {
+    const auto o = before.row(k, r), w = after.row(k, r);
+    const double dA = k.rho0 * (w.dA - o.dA), dV = k.rho0 * (w.V2 - o.V2);  // of the terms with constant factors
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      pair_t x = v[3 * r + c];
+      double df = after.g1[c] * w.A - before.g1[c] * o.A;
+      double dg = (after.g1[c] * w.V1 - before.g1[c] * o.V1) + (after.g2[c] * w.A - before.g2[c] * o.A);
+      if (DEV) {
+        df += k.psi0[0][c] * dA;
+        dg += k.psi0[0][c] * dV + k.b0[0][c] * dA;
+      }
+      x.x = (S)((double)x.x + df);
+      x.y = (S)((double)x.y + dg);
+      *(pair_t*)(at + (3 * r + c) * p.sl) = x;
     }
-    m.omega = m.omega1 = 1.0;
-    m.corr = 0.0;
-    if (w) equilibria<D, double, DEV>(m, d0, k, fn, gn);
-    else equilibria<D, double, DEV>(m, d0, k, fo, go);
-  }
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    S& fi = pops[pop_offset(p, Q, i, n)];
-    S& gi = pops[pop_offset(p, Q, i + Q, n)];
-    fi = (S)((double)fi + (fn[i] - fo[i]));
-    gi = (S)((double)gi + (gn[i] - go[i]));
   }
 }
 
-// new = keep * old + d (rho, u planes, T); d: drho[N], du[D N], dT[N]; keep is
-// 1 (increments) or 0 (new values; u_z of a 2-D lattice stays 0)
-__global__ void __launch_bounds__(256) fields_plus_kernel(const double* __restrict__ oldf, const double* __restrict__ drho,
-                                                          const double* __restrict__ du, const double* __restrict__ dT,
-                                                          double* __restrict__ newf, long long N, int D, int keep) {
-  const long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+// New fields keep * old + d (rho, u, T; d: drho[N], du[D N], dT[N]; keep is 1
+// for increments, 0 for new values; u_z of a 2-D lattice stays 0) of the
+// populations' own fields into the planes of newf, and the count of nodes
+// where they are not finite or rho or T is not positive, per work-group.
+template <int D, typename S>
+__global__ void __launch_bounds__(256) fields_new_kernel(const S* __restrict__ pops, const double* __restrict__ drho,
+                                                         const double* __restrict__ du, const double* __restrict__ dT,
+                                                         double keep, double* __restrict__ newf,
+                                                         double* __restrict__ partial, int N, const StepParams p) {
+  double bad[1] = {0.0};
+  for (long long n = (long long)blockIdx.x * 256 + threadIdx.x; n < N; n += (long long)gridDim.x * 256) {
+    typename Buf<S>::pair_t v[lat_q(D)];
+    load_pairs<D>(pops + pair_offset(p, (int)n), p, v);
+    double s0, j[3], se, rho, u[3], T, rhoE;
+    pair_sums<D>(v, s0, j, &se);
+    fields_of<D>(p, s0, j, se, rho, u, T, rhoE);
+    const double r = keep * rho + drho[n], t = keep * T + dT[n];
+    bool ok = isfinite(r) && isfinite(t) && r > 0.0 && t > 0.0;
+    newf[n] = r;
+    newf[4LL * N + n] = t;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double w = keep * u[a] + (a < D ? du[(long long)a * N + n] : 0.0);
+      if (a < D) ok = ok && isfinite(w);
+      newf[(1LL + a) * N + n] = w;
+    }
+    bad[0] += ok ? 0.0 : 1.0;
+  }
+  block_reduce_store<1, 4>(bad, partial + blockIdx.x, 1);
+}
+
+// rho, u, T as the FP32 input planes x[D + 2][N] of the corrector.
+template <int D, typename S>
+__global__ void __launch_bounds__(256) planes_kernel(const S* __restrict__ pops, float* __restrict__ x, int N,
+                                                     const StepParams p) {
+  const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
-  const double k = keep ? 1.0 : 0.0;
-  newf[n] = k * oldf[n] + drho[n];
-  for (int a = 0; a < 3; ++a) newf[(1 + a) * N + n] = k * oldf[(1 + a) * N + n] + (a < D ? du[a * N + n] : 0.0);
-  newf[4 * N + n] = k * oldf[4 * N + n] + dT[n];
+  typename Buf<S>::pair_t v[lat_q(D)];
+  load_pairs<D>(pops + pair_offset(p, n), p, v);
+  double s0, j[3], se, rho, u[3], T, rhoE;
+  pair_sums<D>(v, s0, j, &se);
+  fields_of<D>(p, s0, j, se, rho, u, T, rhoE);
+  x[n] = (float)rho;
+#pragma unroll
+  for (int a = 0; a < D; ++a) x[(long long)(1 + a) * N + n] = (float)u[a];
+  x[(long long)(1 + D) * N + n] = (float)T;
 }
 
 // Coarse nodes: means of rho, rho u and rho E over factor^D fine nodes,
@@ -1485,33 +1608,62 @@ __global__ void __launch_bounds__(256) filter_kernel(const S* __restrict__ pops,
   T[o] = p.caloric ? caloric_step(p.Cv, p.cv1, p.cv2, 0.0, e) : e / p.Cv;
 }
 
-hipError_t launch_fields_add(const Ctx& c, void* pops, const double* oldf, const double* newf) {
-  const long long N = c.N;
-  const dim3 grid((unsigned)((N + 255) / 256)), block(256);
-  if (c.lattice == 3) {
-    if (c.precision == LBM_FP64)
-      hipLaunchKernelGGL((fields_add_kernel<3, false, double>), grid, block, 0, c.stream, (double*)pops, oldf, newf, N,
-                         c.sp);
-    else
-      hipLaunchKernelGGL((fields_add_kernel<3, true, float>), grid, block, 0, c.stream, (float*)pops, oldf, newf, N,
-                         c.sp);
-  } else {
-    if (c.precision == LBM_FP64)
-      hipLaunchKernelGGL((fields_add_kernel<2, false, double>), grid, block, 0, c.stream, (double*)pops, oldf, newf, N,
-                         c.sp);
-    else
-      hipLaunchKernelGGL((fields_add_kernel<2, true, float>), grid, block, 0, c.stream, (float*)pops, oldf, newf, N,
-                         c.sp);
-  }
+template <int D, typename New>
+static hipError_t launch_add_t(const Ctx& c, void* pops, const New& fresh) {
+  const dim3 grid((unsigned)((c.N + 255) / 256)), block(256);
+  if (c.precision == LBM_FP64)
+    hipLaunchKernelGGL((fields_add_kernel<D, false, double, New>), grid, block, 0, c.stream,
+                       static_cast<double*>(pops), fresh, (int)c.N, c.sp);
+  else
+    hipLaunchKernelGGL((fields_add_kernel<D, true, float, New>), grid, block, 0, c.stream, static_cast<float*>(pops),
+                       fresh, (int)c.N, c.sp);
   return hipGetLastError();
 }
 
-hipError_t launch_fields_plus(const Ctx& c, const double* oldf, const double* drho, const double* du, const double* dT,
-                              double* newf, bool keep) {
-  const long long N = c.N;
-  hipLaunchKernelGGL(fields_plus_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, c.stream, oldf, drho, du, dT,
-                     newf, N, c.lattice, keep ? 1 : 0);
+hipError_t launch_fields_add(const Ctx& c, void* pops, const double* newf) {
+  const NewFields fresh{newf, c.N};
+  return c.lattice == 3 ? launch_add_t<3>(c, pops, fresh) : launch_add_t<2>(c, pops, fresh);
+}
+
+hipError_t launch_correct(const Ctx& c, void* pops, const float* y, const float* sd, int channels, int offset,
+                          float limit) {
+  if (c.lattice == 3) return launch_add_t<3>(c, pops, Corrected<3>{y, sd, channels, offset, limit, c.N});
+  return launch_add_t<2>(c, pops, Corrected<2>{y, sd, channels, offset, limit, c.N});
+}
+
+template <int D, typename S>
+static void launch_new_t(const Ctx& c, const void* pops, const double* drho, const double* du, const double* dT,
+                         bool keep, double* newf, double* partial, int nblocks) {
+  hipLaunchKernelGGL((fields_new_kernel<D, S>), dim3(nblocks), dim3(256), 0, c.stream, static_cast<const S*>(pops),
+                     drho, du, dT, keep ? 1.0 : 0.0, newf, partial, (int)c.N, c.sp);
+}
+
+hipError_t launch_fields_new(const Ctx& c, const void* pops, const double* drho, const double* du, const double* dT,
+                             bool keep, double* newf, double* partial, int nblocks, double* out) {
+  if (c.lattice == 3) {
+    if (c.precision == LBM_FP64) launch_new_t<3, double>(c, pops, drho, du, dT, keep, newf, partial, nblocks);
+    else launch_new_t<3, float>(c, pops, drho, du, dT, keep, newf, partial, nblocks);
+  } else {
+    if (c.precision == LBM_FP64) launch_new_t<2, double>(c, pops, drho, du, dT, keep, newf, partial, nblocks);
+    else launch_new_t<2, float>(c, pops, drho, du, dT, keep, newf, partial, nblocks);
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(final_reduce_kernel, dim3(1), dim3(256), 0, c.stream, partial, nblocks, out);
   return hipGetLastError();
+}
+
+template <int D, typename S>
+static hipError_t launch_planes_t(const Ctx& c, const void* pops, float* x) {
+  hipLaunchKernelGGL((planes_kernel<D, S>), dim3((unsigned)((c.N + 255) / 256)), dim3(256), 0, c.stream,
+                     static_cast<const S*>(pops), x, (int)c.N, c.sp);
+  return hipGetLastError();
+}
+
+hipError_t launch_planes(const Ctx& c, const void* pops, float* x) {
+  if (c.lattice == 3)
+    return c.precision == LBM_FP64 ? launch_planes_t<3, double>(c, pops, x) : launch_planes_t<3, float>(c, pops, x);
+  return c.precision == LBM_FP64 ? launch_planes_t<2, double>(c, pops, x) : launch_planes_t<2, float>(c, pops, x);
 }
 
 template <int D, typename S>

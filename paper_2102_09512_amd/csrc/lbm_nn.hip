@@ -693,27 +693,6 @@ __global__ void __launch_bounds__(256) fields_to_input_kernel(const double* __re
   x[(size_t)(1 + D) * V + v] = (float)T[v];
 }
 
-// normalised correction planes -> FP64 increments drho[V], du[D V], dT[V]:
-// output c corrects field off + c (0 rho, 1..D u, D + 1 T); fields without an
-// output get a zero increment; with limit > 0 the normalised output is
-// clipped to [-limit, limit] first
-__global__ void __launch_bounds__(256) output_to_increments_kernel(const float* __restrict__ y,
-                                                                   const float* __restrict__ sd, int C, int off, int D,
-                                                                   float limit, int V, double* __restrict__ drho,
-                                                                   double* __restrict__ du, double* __restrict__ dT) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= V) return;
-  for (int fld = 0; fld < D + 2; ++fld) {
-    const int c = fld - off;
-    float yc = (c >= 0 && c < C) ? y[(size_t)c * V + v] : 0.f;
-    if (limit > 0.f) yc = fminf(fmaxf(yc, -limit), limit);
-    const double inc = (c >= 0 && c < C) ? (double)yc * sd[c] : 0.0;
-    if (fld == 0) drho[v] = inc;
-    else if (fld <= D) du[(size_t)(fld - 1) * V + v] = inc;
-    else dT[v] = inc;
-  }
-}
-
 }  // namespace lbmnn
 
 // ---------------------------------------------------------------------------
@@ -766,8 +745,7 @@ struct lbm_nn_ctx {
   double* lpart = nullptr;              // loss partials
   double* loss_acc = nullptr;           // running sum of asynchronous losses (device, 1 value)
   long long loss_count = 0;             // losses added to it since the last lbm_nn_take_loss
-  float* fld = nullptr;                 // corrector staging: fields and correction (FP32)
-  double* dfld = nullptr;               // FP64 fields / increments for lbm
+  float* fld = nullptr;                 // the corrector's input planes
 };
 
 namespace {
@@ -906,7 +884,6 @@ int lbm_nn_create(lbm_nn* out, int layers, const int* channels, const int64_t di
   alloc((void**)&n->lpart, sizeof(double) * (size_t)((V + 255) / 256));
   alloc((void**)&n->loss_acc, sizeof(double));
   alloc((void**)&n->fld, sizeof(float) * 16 * (size_t)V);
-  alloc((void**)&n->dfld, sizeof(double) * 10 * (size_t)V);
   for (int l = 0; l < layers; ++l) {
     Layer& ly = n->layers[l];
     alloc((void**)&ly.wp, sizeof(__bf16) * 27 * ly.cinp * 32);
@@ -946,7 +923,7 @@ int lbm_nn_destroy(lbm_nn n) {
   if (n->stream) (void)hipStreamSynchronize(n->stream);
   for (void* p : {(void*)n->params, (void*)n->grads, (void*)n->m, (void*)n->v, (void*)n->mean, (void*)n->inv_std,
                   (void*)n->out_std, (void*)n->inv_out_std, (void*)n->dA, (void*)n->dB, (void*)n->y, (void*)n->part, (void*)n->part2, (void*)n->lpart,
-                  (void*)n->loss_acc, (void*)n->fld, (void*)n->dfld})
+                  (void*)n->loss_acc, (void*)n->fld})
     if (p) (void)hipFree(p);
   for (__bf16* p : n->act)
     if (p) (void)hipFree(p);
@@ -1163,28 +1140,13 @@ int lbm_nn_correct(lbm_nn n, lbm_handle h) {
     return nn_fail(LBM_EINVAL, "lbm_nn_correct: grid of the handle differs from the network's");
   int rc = nn_select(n);
   if (rc) return rc;
-  const int V = n->V;
-  double* drho = n->dfld;
-  double* du = drho + V;
-  double* dT = du + 3 * (size_t)V;
-  // everything on the handle's stream: moments, network, increments
+  // everything on the handle's stream: planes, network, re-equilibration
   hipStream_t saved = n->stream;
   n->stream = h->stream;
-  if ((rc = lbm::fields_current(h)) == LBM_OK) {
-    const double* F = h->fields;  // rho, u_x, u_y, u_z, T, rho E planes
-    hipLaunchKernelGGL(lbmnn::fields_to_input_kernel, dim3((V + 255) / 256), dim3(256), 0, n->stream, F, F + V,
-                       F + 4 * (size_t)V, D, V, n->fld);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) rc = nn_hip(e, "fields kernel");
-    if (rc == LBM_OK) rc = nn_forward(n, n->fld, nullptr, false);
-    if (rc == LBM_OK) {
-      hipLaunchKernelGGL(lbmnn::output_to_increments_kernel, dim3((V + 255) / 256), dim3(256), 0, n->stream, n->y,
-                         n->out_std, n->ch[n->L], n->out_off, D, (float)n->limit, V, drho, du, dT);
-      e = hipGetLastError();
-      if (e != hipSuccess) rc = nn_hip(e, "increments kernel");
-    }
-    if (rc == LBM_OK) rc = lbm::fields_increment_async(h, drho, du, dT);
-  }
+  rc = lbm::corrector_planes(h, n->fld);
+  if (rc == LBM_OK) rc = nn_forward(n, n->fld, nullptr, false);
+  if (rc == LBM_OK)
+    rc = lbm::corrector_apply(h, n->y, n->out_std, n->ch[n->L], n->out_off, (float)n->limit);
   n->stream = saved;
   return rc;
 }
