@@ -93,6 +93,7 @@ constexpr int kScratchDoubles = kMaxDiagBlocks * kNumDiag + kNumDiag;
 struct DiagGrid {
   int by;  // y width of the tile (D3Q27)
   int tiles_x, tiles_y, chunk, tasks, blocks;
+  bool flat;  // 256 nodes in memory order instead of tiles
 };
 
 // One box of a batched launch (an entry of the device box table).

@@ -929,13 +929,16 @@ __global__ void __launch_bounds__(BX* BY) diag_kernel(const S* __restrict__ pops
     };
     double up[3] = {}, uc[3] = {}, un[3] = {};  // velocity at m - 1, m, m + 1
     double mu = 0, mu_n = 0;
-    if (active) velocity(m0 - 1, core, up);
+    if (active) {  // a one-plane chunk asks for both neighbours before the barrier
+      velocity(m0 - 1, core, up);
+      if (m0 + 1 == m1) velocity(m1, core, un);
+    }
     fill(m0, 0, uc, mu);
     __syncthreads();
     for (int m = m0; m < m1; ++m) {
       const int cb = (m - m0) & 1;
       if (m + 1 < m1) fill(m + 1, cb ^ 1, un, mu_n);
-      else if (active) velocity(m + 1, core, un);
+      else if (m > m0 && active) velocity(m + 1, core, un);
       if (active) {
         double vn[6][3] = {};
         const int yy = (D == 3) ? ly + 1 : 0;
@@ -964,6 +967,70 @@ __global__ void __launch_bounds__(BX* BY) diag_kernel(const S* __restrict__ pops
   double v[kNumDiag];
   sums.store(v);
   block_reduce_store<kNumDiag, BX * BY / 64>(v, partial + blockIdx.x, gridDim.x);
+}
+
+// The same sums for boxes so narrow that a tile would leave most of its lanes
+// idle: 256 nodes in memory order, whose velocities go to LDS; a neighbour
+// that is not among them is formed again from its populations.  Bound by
+// those loads: a velocity costs Q pairs where the marching kernel reads LDS.
+template <int D, typename S>
+__global__ void __launch_bounds__(256) diag_flat_kernel(const S* __restrict__ pops, double* __restrict__ partial,
+                                                        int N, const StepParams p) {
+  constexpr int Q = lat_q(D);
+  __shared__ double lu[D][256];
+  const int t = threadIdx.x;
+  const int n0 = p.nx, n1 = p.ny, n2 = (D == 3) ? p.nz : 1;
+  DiagSums<D> sums;
+  // Work-groups go round the eight dies: each die takes one stretch of the
+  // box, whose planes its cache then serves three times (300 x 3 x 400 FP64:
+  // 130 us a call against 175 with the tiles dealt out in turn).
+  const int tiles = (int)(((long long)N + 255) / 256), per = (tiles + 7) / 8, die = blockIdx.x & 7;
+  const int last = min((die + 1) * per, tiles);
+  for (int tile = die * per + (blockIdx.x >> 3); tile < last; tile += gridDim.x >> 3) {
+    const long long base = (long long)tile * 256;
+    const bool active = base + t < N;
+    const int n = active ? (int)(base + t) : N - 1;
+    const int x = n % n0, r = n / n0, y = (D == 3) ? r % n1 : r, z = (D == 3) ? r / n1 : 0;
+    double rho, u[3], T, rhoE;
+    {
+      typename Buf<S>::pair_t v[Q];
+      double s0, j[3], se;
+      load_pairs<D>(pops + pair_offset(p, n), p, v);
+      pair_sums<D>(v, s0, j, &se);
+      fields_of<D>(p, s0, j, se, rho, u, T, rhoE);
+    }
+#pragma unroll
+    for (int a = 0; a < D; ++a) lu[a][t] = u[a];
+    __syncthreads();
+    if (active) {
+      sums.of_node(p, rho, u, T, rhoE);
+      const double mu = (p.visc_exp == 0.0) ? p.mu0 : p.mu0 * pow(T * p.inv_Tref, p.visc_exp);
+      double vn[6][3] = {};
+#pragma unroll
+      for (int k = 0; k < 2 * D; ++k) {
+        const int step = (k & 1) ? -1 : 1;
+        int q = k < 2   ? n - x + fix_near(x + step, n0, p.bc[0])
+                : k < 4 ? n + (fix_near(y + step, n1, p.bc[1]) - y) * n0
+                        : n + (fix_near(z + step, n2, p.bc[2]) - z) * p.plane;
+        const long long at = q - base;
+        if (at >= 0 && at < 256) {
+#pragma unroll
+          for (int a = 0; a < D; ++a) vn[k][a] = lu[a][at];
+        } else {
+          typename Buf<S>::pair_t v[Q];
+          double s0, j[3];
+          load_pairs<D>(pops + pair_offset(p, q), p, v);
+          pair_sums<D>(v, s0, j, nullptr);
+          velocity_of<D>(p, s0, j, vn[k]);
+        }
+      }
+      sums.of_differences(mu, vn);
+    }
+    __syncthreads();
+  }
+  double v[kNumDiag];
+  sums.store(v);
+  block_reduce_store<kNumDiag, 4>(v, partial + blockIdx.x, gridDim.x);
 }
 
 // out[j] = the sum of partial[j * nblocks ..]: one work-group per sum, so the
@@ -1709,30 +1776,48 @@ int validate_blocks(const Ctx& c) {
 
 // Work-groups and march chunks of the diagnostics: 64 x 8 tiles (a smaller
 // ring to read again: 890 us at 256^3 FP32 against 1030 for 64 x 4) as long as
-// they leave every compute unit a work-group, else 64 x 4; chunks as long as
-// that allows, as each reads two more planes, but of at least 4.
+// they leave every compute unit a work-group with chunks of four planes, else
+// 64 x 4; 128 x 1 in 2-D (2000 x 1500 FP64: 116 us a call against 129 for
+// 256 x 1, which also leaves more lanes idle past a ragged edge).  Chunks are
+// as long as `target` work-groups allow, as each reads two more planes, and
+// shorter than four planes only where the grid cannot fill the chip: there
+// the chain of planes is the time (a call on 12^3: 36 us with one-plane
+// chunks against 45 with four; on 100 x 60: 32 against 37; but 59 against 49
+// on 50 x 60 x 40 in FP64, which has 600 tile planes).  A box whose planes use
+// less than 0.4 (FP32) or 0.25 (FP64) of a tile's lanes goes in memory order:
+// calls on 5 x 400 x 300 take 117 and 162 us against 372 and 391 in tiles, on
+// 20 x 200 x 200 (a share of 0.31) 136 and 223 against 158 and 209.
 DiagGrid diag_grid(const Ctx& c) {
   DiagGrid g{};
   const int64_t nm = c.lattice == 3 ? c.n[2] : c.n[1];
-  auto shape = [&](int bx, int by, int64_t target) {
+  auto shape = [&](int bx, int by, int64_t target, int64_t fill) {
     g.by = by;
     g.tiles_x = (int)((c.n[0] + bx - 1) / bx);
     g.tiles_y = c.lattice == 3 ? (int)((c.n[1] + by - 1) / by) : 1;
     const int64_t tiles = (int64_t)g.tiles_x * g.tiles_y;
     const int64_t chunks = tiles < target ? target / tiles : 1;
     int64_t chunk = (nm + chunks - 1) / chunks;
-    if (chunk < 4) chunk = nm < 4 ? nm : 4;
+    const int64_t least = std::min<int64_t>((tiles * nm + fill - 1) / fill, 4);
+    if (chunk < least) chunk = least;
     g.chunk = (int)chunk;
     const int64_t tasks = tiles * ((nm + chunk - 1) / chunk);
     g.tasks = (int)tasks;
     g.blocks = (int)(tasks < kMaxDiagBlocks ? tasks : kMaxDiagBlocks);
   };
-  if (c.lattice == 2) {
-    shape(256, 1, 1024);
+  const int bx = c.lattice == 3 ? 64 : 128, by = c.lattice == 3 ? 4 : 1;
+  const int64_t plane = c.n[0] * (c.lattice == 3 ? c.n[1] : 1);
+  const int64_t lanes = (c.n[0] + bx - 1) / bx * bx * (c.lattice == 3 ? (c.n[1] + by - 1) / by * by : 1);
+  if ((double)plane < (c.precision == LBM_FP64 ? 0.25 : 0.4) * (double)lanes) {
+    g.flat = true;
+    g.blocks = (validate_blocks(c) + 7) / 8 * 8;
     return g;
   }
-  shape(64, 8, 256);
-  if (g.tasks < 256) shape(64, 4, 1024);
+  if (c.lattice == 2) {
+    shape(128, 1, 1024, 1024);
+    return g;
+  }
+  shape(64, 8, 256, 256);
+  if (g.tasks < 256 || (g.chunk < 4 && g.chunk < nm)) shape(64, 4, 1024, 256);
   return g;
 }
 
@@ -1756,8 +1841,22 @@ static void launch_diag_t(const Ctx& c, const void* pops, double* partial, const
                      static_cast<const S*>(pops), partial, c.sp, g);
 }
 
+template <int D, typename S>
+static void launch_diag_flat(const Ctx& c, const void* pops, double* partial, const DiagGrid& g) {
+  hipLaunchKernelGGL((diag_flat_kernel<D, S>), dim3(g.blocks), dim3(256), 0, c.stream, static_cast<const S*>(pops),
+                     partial, (int)c.N, c.sp);
+}
+
 hipError_t launch_diag(const Ctx& c, const void* pops, double* partial, const DiagGrid& g, double* out) {
-  if (c.lattice == 3) {
+  if (g.flat) {
+    if (c.lattice == 3) {
+      if (c.precision == LBM_FP64) launch_diag_flat<3, double>(c, pops, partial, g);
+      else launch_diag_flat<3, float>(c, pops, partial, g);
+    } else {
+      if (c.precision == LBM_FP64) launch_diag_flat<2, double>(c, pops, partial, g);
+      else launch_diag_flat<2, float>(c, pops, partial, g);
+    }
+  } else if (c.lattice == 3) {
     if (c.precision == LBM_FP64) {
       if (g.by == 8) launch_diag_t<3, double, 64, 8>(c, pops, partial, g);
       else launch_diag_t<3, double, 64, 4>(c, pops, partial, g);
@@ -1766,9 +1865,9 @@ hipError_t launch_diag(const Ctx& c, const void* pops, double* partial, const Di
       else launch_diag_t<3, float, 64, 4>(c, pops, partial, g);
     }
   } else if (c.precision == LBM_FP64) {
-    launch_diag_t<2, double, 256, 1>(c, pops, partial, g);
+    launch_diag_t<2, double, 128, 1>(c, pops, partial, g);
   } else {
-    launch_diag_t<2, float, 256, 1>(c, pops, partial, g);
+    launch_diag_t<2, float, 128, 1>(c, pops, partial, g);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

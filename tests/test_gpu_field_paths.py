@@ -9,10 +9,14 @@ from paper_2102_09512_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-# 64 x 8 and 64 x 4 (D3Q27) and 256 x 1 (D2Q9) tiles: one node, below, at and
+# 64 x 8 and 64 x 4 (D3Q27) and 128 x 1 (D2Q9) tiles: one node, below, at and
 # just past the tile edges, several chunks, several work-group shapes
 DIMS = [(2, (1, 1)), (2, (255, 3)), (2, (257, 33)), (2, (64, 700)), (3, (1, 1, 1)), (3, (64, 8, 5)), (3, (65, 9, 4)),
         (3, (63, 7, 70)), (3, (129, 33, 40)), (3, (200, 130, 37))]
+# narrow boxes, taken 256 nodes at a time in memory order: neighbours within
+# and outside the 256, remainders, more nodes than one pass of the work-groups
+DIMS += [(2, (3, 85)), (2, (20, 300)), (2, (3, 180000)), (3, (1, 1, 257)), (3, (3, 3, 400)), (3, (300, 1, 9)),
+         (3, (1, 300, 5)), (3, (5, 30, 20)), (3, (12, 250, 190))]
 
 
 def _sums(D, rho, u, T, clamp, mu, visc_exp, T_ref, cv):
