@@ -244,14 +244,18 @@ __global__ void __launch_bounds__(64 * kW) conv_kernel(const __bf16* __restrict_
 // conv_kernel (bf16 [v][32]).  PLANAR_IN: the input is read straight from
 // the FP32 planes x[c][v] (c < cin) and normalised as pack_input_kernel does
 // (the same expression, so the staged bf16 values are the same), for calls
-// that need no packed copy of it (inference).
+// that need no packed copy of it (inference).  Otherwise in holds `stride`
+// channels per node.  The gradient of an output layer of at most 8 channels
+// goes back through it too: stride 8, the mirrored weights and the ReLU
+// derivative's mask (64^3: 13.5 us; as 32 channels through conv_kernel 20.8).
 template <bool PLANAR_IN>
-__global__ void __launch_bounds__(64 * kW) conv_pair_kernel(const __bf16* __restrict__ in,
+__global__ void __launch_bounds__(64 * kW) conv_pair_kernel(const __bf16* __restrict__ in, int stride,
                                                             const float* __restrict__ x, int cin,
                                                             const float* __restrict__ mean,
                                                             const float* __restrict__ inv_std,
                                                             const __bf16* __restrict__ wq,
                                                             const float* __restrict__ bias, int relu,
+                                                            const __bf16* __restrict__ mask,
                                                             __bf16* __restrict__ out, int cout, const Grid g, int V) {
   constexpr int NN = kHZ * kHY * kHX;  // halo nodes; one 16-byte chunk each
   __shared__ __attribute__((aligned(16))) __bf16 tile[NN * 8];
@@ -327,7 +331,7 @@ __global__ void __launch_bounds__(64 * kW) conv_pair_kernel(const __bf16* __rest
       if (node < NN) {
         const int hx = node % kHX, hy = (node / kHX) % kHY, hz = node / (kHX * kHY);
         const int gx = wrap(x0 + hx - 1, g.nx), gy = wrap(y0 + hy - 1, g.ny), gz = wrap(z0 + hz - 1, g.nz);
-        stage[k] = *(const bf8*)(in + ((size_t)gx + (size_t)g.nx * (gy + (size_t)g.ny * gz)) * 16);
+        stage[k] = *(const bf8*)(in + ((size_t)gx + (size_t)g.nx * (gy + (size_t)g.ny * gz)) * stride);
       }
     }
 #pragma unroll
@@ -350,7 +354,7 @@ __global__ void __launch_bounds__(64 * kW) conv_pair_kernel(const __bf16* __rest
       acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[p], bv, acc[j], 0, 0, 0);
     }
   }
-  conv_epilogue<false>(acc, bo, relu, nullptr, out, cout, g, V, x0, y0, z0, w, r, half);
+  conv_epilogue<false>(acc, bo, relu, mask, out, cout, g, V, x0, y0, z0, w, r, half);
 }
 
 // Output layer with at most 16 channels (the corrector's 3): the same
@@ -452,6 +456,31 @@ constexpr int kGMaxBlocks = 256;
 
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
 
+// Channel j of two neighbouring nodes as one word of channel-major LDS, eight
+// channels.
+__device__ inline void transpose(const u4 (&v)[2], __bf16* dst, int plane) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const unsigned a = v[0][j / 2], b = v[1][j / 2];
+    *(unsigned*)(dst + j * plane) =
+        j % 2 ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
+  }
+}
+
+// The 8 elements from element o (0, 1 or 2) of lo.
+__device__ inline bf8 shifted(const u4& lo, const u4& hi, int o) {
+  u4 v;
+  if (o == 0) {
+    v = lo;
+  } else if (o == 2) {
+    v = u4{lo.y, lo.z, lo.w, hi.x};
+  } else {
+    v = u4{__builtin_amdgcn_alignbit(lo.y, lo.x, 16), __builtin_amdgcn_alignbit(lo.z, lo.y, 16),
+           __builtin_amdgcn_alignbit(lo.w, lo.z, 16), __builtin_amdgcn_alignbit(hi.x, lo.w, 16)};
+  }
+  return __builtin_bit_cast(bf8, v);
+}
+
 template <int CIN>
 __global__ void __launch_bounds__(512) wgrad_kernel(const __bf16* __restrict__ in, const __bf16* __restrict__ dout,
                                                     float* __restrict__ part, const Grid g, int ntiles, int tpb,
@@ -494,15 +523,6 @@ __global__ void __launch_bounds__(512) wgrad_kernel(const __bf16* __restrict__ i
         for (int q = 0; q < 2; ++q)
           si[k][q] = *(const u4*)(base + (size_t)wrap(x0 + 2 * pair + q - 1, g.nx) * CIN);
       }
-    }
-  };
-  // Channel j of both nodes of an item as one word, eight channels.
-  auto transpose = [&](const u4 (&v)[2], __bf16* dst, int plane) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const unsigned a = v[0][j / 2], b = v[1][j / 2];
-      *(unsigned*)(dst + j * plane) =
-          j % 2 ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
     }
   };
   int tile = first + half_wg;
@@ -561,18 +581,6 @@ __global__ void __launch_bounds__(512) wgrad_kernel(const __bf16* __restrict__ i
           lo = *(const u4*)src;
           hi = *(const u4*)(src + 8);
         };
-        auto shifted = [&](const u4& lo, const u4& hi, int o) {  // the 8 elements from element o of lo
-          u4 v;
-          if (o == 0) {
-            v = lo;
-          } else if (o == 2) {
-            v = u4{lo.y, lo.z, lo.w, hi.x};
-          } else {
-            v = u4{__builtin_amdgcn_alignbit(lo.y, lo.x, 16), __builtin_amdgcn_alignbit(lo.z, lo.y, 16),
-                   __builtin_amdgcn_alignbit(lo.w, lo.z, 16), __builtin_amdgcn_alignbit(hi.x, lo.w, 16)};
-          }
-          return __builtin_bit_cast(bf8, v);
-        };
 #pragma unroll
         for (int gp = 0; gp < 2; ++gp) {
           u4 lo{}, hi{};
@@ -624,6 +632,143 @@ __global__ void __launch_bounds__(512) wgrad_kernel(const __bf16* __restrict__ i
   }
 }
 
+// The same partials for an output layer of at most 8 channels (dout bf16
+// [v][8], in [v][32]).  The product is turned round: the 32 rows are the input
+// channels of the tile's own nodes u, and the 32 columns are four taps times 8
+// output channels at u - s_t, so that nine columns' worth of (dy, dz) pairs
+// per dx take three products where a tap at a time takes nine, the input needs
+// no halo and the output gradient's is four times smaller.  Waves 0 to 2 of a
+// half own dx = -1, 0, 1; wave 3 owns the bias (a product with ones).
+// 64^3, 32 to 3 channels: 15.5 us (17.9 with one work-group per compute unit;
+// 27.4 in wgrad_kernel).  Two work-groups fit a compute unit, and the partials
+// of so few channels cost little.
+constexpr int kNMaxBlocks = 512;
+
+__global__ void __launch_bounds__(512) wgrad_narrow_kernel(const __bf16* __restrict__ in,
+                                                           const __bf16* __restrict__ dout, float* __restrict__ part,
+                                                           const Grid g, int ntiles, int tpb, int cin, int cout) {
+  constexpr int kHalf = 32 * kGPlaneD + 8 * kGPlaneIn;  // bf16 elements of one half's tile
+  static_assert(4 * 3 * 16 * 64 * sizeof(float) <= 2 * kHalf * sizeof(__bf16), "the halves' sums fit the tiles' LDS");
+  __shared__ __attribute__((aligned(16))) __bf16 lds[2 * kHalf];
+  const int half_wg = threadIdx.x >> 8, t = threadIdx.x & 255;
+  __bf16* inT = lds + half_wg * kHalf;
+  __bf16* dT = inT + 32 * kGPlaneD;
+  const int lane = t & 63, w = t >> 6;
+  const int r = lane & 31, half = lane >> 5;
+  const int tx = g.nx / kGX, ty = g.ny / kGY;
+  bf8 ones;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ones[j] = (__bf16)1.f;
+  f16v acc[3] = {};
+  const int bl = xcd_tile(blockIdx.x, gridDim.x);
+  const int first = bl * tpb, last = min(first + tpb, ntiles);
+  // items of two x neighbours times 8 channels
+  constexpr int NIN = (kGX / 2) * kGY * kGZ * 4, NITI = NIN / 256;
+  constexpr int ND = (kGHX / 2) * kGHY * kGHZ, NITD = (ND + 255) / 256;
+  static_assert(NIN % 256 == 0 && kGHX % 2 == 0, "whole items");
+  u4 si[NITI][2], sd[NITD][2];
+  auto request = [&](int tile) {
+    const int x0 = (tile % tx) * kGX, y0 = ((tile / tx) % ty) * kGY, z0 = (tile / (tx * ty)) * kGZ;
+#pragma unroll
+    for (int k = 0; k < NITI; ++k) {
+      const int e = t + k * 256;
+      const int pair = e % (kGX / 2), c8 = (e / (kGX / 2)) % 4, row = e / (kGX / 2 * 4);
+      const __bf16* base =
+          in + ((size_t)(x0 + 2 * pair) + (size_t)g.nx * (y0 + row % kGY + g.ny * (z0 + row / kGY))) * 32 + 8 * c8;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) si[k][q] = *(const u4*)(base + q * 32);
+    }
+#pragma unroll
+    for (int k = 0; k < NITD; ++k) {
+      const int e = t + k * 256;
+      if (e < ND) {
+        const int pair = e % (kGHX / 2), row = e / (kGHX / 2);
+        const int gy = wrap(y0 + row % kGHY - 1, g.ny), gz = wrap(z0 + row / kGHY - 1, g.nz);
+        const __bf16* base = dout + (size_t)(g.nx * (gy + g.ny * gz)) * 8;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) sd[k][q] = *(const u4*)(base + (size_t)wrap(x0 + 2 * pair + q - 1, g.nx) * 8);
+      }
+    }
+  };
+  int tile = first + half_wg;
+  if (tile < last) request(tile);
+  for (int step = 0; step < tpb; step += 2, tile += 2) {  // the same number of steps in both halves
+    const bool active = tile < last;
+    __syncthreads();  // every wave is done with the previous tiles
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < NITI; ++k) {
+        const int e = t + k * 256;
+        const int pair = e % (kGX / 2), c8 = (e / (kGX / 2)) % 4, row = e / (kGX / 2 * 4);
+        transpose(si[k], inT + 8 * c8 * kGPlaneD + row * kGX + 2 * pair, kGPlaneD);
+      }
+#pragma unroll
+      for (int k = 0; k < NITD; ++k) {
+        const int e = t + k * 256;
+        if (e < ND) transpose(sd[k], dT + e / (kGHX / 2) * kGRow + 2 * (e % (kGHX / 2)), kGPlaneIn);
+      }
+    }
+    __syncthreads();
+    if (tile + 2 < last) request(tile + 2);
+    if (!active) continue;
+#pragma unroll 1
+    for (int row = 0; row < kGY * kGZ; ++row) {
+      const int yy = row % kGY, zz = row / kGY;
+#pragma unroll
+      for (int kb = 0; kb < kGX; kb += 16) {
+        auto column = [&](int pair, int shift) {  // output channel r % 8 at u - s of these nodes
+          const int dy = pair % 3 - 1, dz = pair / 3 - 1;
+          const __bf16* src =
+              dT + (r & 7) * kGPlaneIn + ((zz - dz + 1) * kGHY + yy - dy + 1) * kGRow + kb + 8 * half;
+          return shifted(*(const u4*)src, *(const u4*)(src + 8), shift);
+        };
+        if (w < 3) {
+          const bf8 a = *(const bf8*)(inT + r * kGPlaneD + row * kGX + kb + 8 * half);
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, column(min(4 * j + (r >> 3), 8), 2 - w), acc[j], 0, 0, 0);
+        } else {
+          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, column(4, 1), acc[0], 0, 0, 0);
+        }
+      }
+    }
+  }
+  // the second half's sums through LDS into the first half's
+  if (tpb > 1) {
+    __syncthreads();
+    float* sums = (float*)lds + (w * 3 * 16) * 64 + lane;
+    if (half_wg == 1) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sums[(k * 16 + i) * 64] = acc[k][i];
+    }
+    __syncthreads();
+    if (half_wg == 0) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[k][i] += sums[(k * 16 + i) * 64];
+    }
+  }
+  if (half_wg) return;
+  // accumulator i of lane l holds row m = 8(i/4) + 4(l/32) + i%4, column r = l%32
+  const int o = r & 7;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int pair = 4 * k + (r >> 3);
+    const bool bias = w == 3 && k == 0 && r < 8;
+    if (o >= cout || !(bias || (w < 3 && pair < 9))) continue;
+    const int slot = w == 3 ? 27 : 3 * pair + w;
+    float* dst = part + ((size_t)slot * gridDim.x + bl) * cin * cout;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int m = 8 * (i >> 2) + 4 * half + (i & 3);
+      if (m < cin) dst[m * cout + o] = acc[k][i];
+    }
+  }
+}
+
 // grad[t][i][o] += sum_b part[t][b][i][o] (t < 27) and grad_b[o] += sum_b
 // part[27][b][0][o], part laid out [28][nblk][cin][cout].  A work-group takes 64
 // consecutive (i, o) of one slot; its wavefront s adds the s-th of sixteen equal
@@ -660,7 +805,8 @@ __global__ void __launch_bounds__(64 * kGRuns) wgrad_sum_kernel(const float* __r
 }
 
 // r_c = y_c + (x_f - target_f) / out_std_c with f = off + c; loss partial sums
-// of r^2; dout[v][c] = 2 r / (C V)
+// of r^2; dout[v][c] = 2 r / (C V), of 32 channels or, for C <= 8, of 8
+template <int CH>
 __global__ void __launch_bounds__(256) loss_kernel(const float* __restrict__ y, const float* __restrict__ x,
                                                    const float* __restrict__ tgt, const float* __restrict__ inv_std,
                                                    int C, int off, int V, __bf16* __restrict__ dout,
@@ -670,9 +816,9 @@ __global__ void __launch_bounds__(256) loss_kernel(const float* __restrict__ y, 
   double s = 0.0;
   if (v < V) {
     const float scale = 2.f / ((float)C * (float)V);
-    bf8 o[4];  // the node's 32 gradient channels, stored as four 16-byte words
+    bf8 o[CH / 8];  // the node's gradient channels, stored as 16-byte words
 #pragma unroll
-    for (int c = 0; c < 32; ++c) {
+    for (int c = 0; c < CH; ++c) {
       float g = 0.f;
       if (c < C) {
         const size_t f = (size_t)(off + c) * V + v;
@@ -683,7 +829,7 @@ __global__ void __launch_bounds__(256) loss_kernel(const float* __restrict__ y, 
       o[c / 8][c % 8] = (__bf16)g;
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) *(bf8*)(dout + (size_t)v * 32 + 8 * q) = o[q];
+    for (int q = 0; q < CH / 8; ++q) *(bf8*)(dout + (size_t)v * CH + 8 * q) = o[q];
   }
   red[threadIdx.x] = s;
   __syncthreads();
@@ -728,10 +874,12 @@ __global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ p, const 
 // wb[t][o/16][i][o%16] = W[26 - t][i][o] (32 padded outputs as inputs, 32 rows)
 // and, for an output layer of at most 16 channels, wn[t][o][i] = W[t][i][o]
 // (16 padded outputs, 32 padded inputs); for an input layer of at most 8
-// channels, wq[p][o][k] (taps 2p and 2p + 1, 8 channels each)
+// channels, wq[p][o][k] (taps 2p and 2p + 1, 8 channels each); for an output
+// layer of at most 8, wr[p][i][k] the same of the mirrored convolution
 __global__ void __launch_bounds__(256) pack_weights_kernel(const float* __restrict__ W, int cin, int cout, int cinp,
                                                            __bf16* __restrict__ wp, __bf16* __restrict__ wb,
-                                                           __bf16* __restrict__ wn, __bf16* __restrict__ wq) {
+                                                           __bf16* __restrict__ wn, __bf16* __restrict__ wq,
+                                                           __bf16* __restrict__ wr) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e < 27 * cinp * 32) {  // wp element (t, cc, o, k)
     const int k = e % 16, o = (e / 16) % 32, cc = (e / 512) % (cinp / 16), t = e / (512 * (cinp / 16));
@@ -742,6 +890,11 @@ __global__ void __launch_bounds__(256) pack_weights_kernel(const float* __restri
     const int k = e % 16, o = (e / 16) % 32, p = e / 512;
     const int t = 2 * p + k / 8, i = k % 8;
     wq[e] = (__bf16)(t < 27 && i < cin && o < cout ? W[((size_t)t * cin + i) * cout + o] : 0.f);
+  }
+  if (wr && e < 14 * 32 * 16) {  // wr element (p, i, k): tap 2p + k / 8, output channel k % 8
+    const int k = e % 16, i = (e / 16) % 32, p = e / 512;
+    const int t = 2 * p + k / 8, o = k % 8;
+    wr[e] = (__bf16)(t < 27 && i < cin && o < cout ? W[((size_t)(26 - t) * cin + i) * cout + o] : 0.f);
   }
   if (wn && e < 27 * 16 * 32) {  // wn element (t, o, i)
     const int i = e % 32, o = (e / 32) % 16, t = e / 512;
@@ -791,6 +944,7 @@ struct Layer {
   __bf16 *wp = nullptr, *wb = nullptr;
   __bf16* wn = nullptr;         // output layer of <= 16 channels from 32 inputs: weights for conv_narrow_kernel
   __bf16* wq = nullptr;         // input layer of <= 8 channels (not the last): weights for conv_pair_kernel
+  __bf16* wr = nullptr;         // output layer of <= 8 channels (not the first): mirrored, for conv_pair_kernel
 };
 
 }  // namespace
@@ -833,7 +987,7 @@ int nn_pack_weights(lbm_nn n) {
     Layer& ly = n->layers[l];
     const int total = 27 * 32 * 32 > 27 * ly.cinp * 32 ? 27 * 32 * 32 : 27 * ly.cinp * 32;
     hipLaunchKernelGGL(lbmnn::pack_weights_kernel, dim3((total + 255) / 256), dim3(256), 0, n->stream,
-                       n->params + ly.w_off, ly.cin, ly.cout, ly.cinp, ly.wp, l > 0 ? ly.wb : nullptr, ly.wn, ly.wq);
+                       n->params + ly.w_off, ly.cin, ly.cout, ly.cinp, ly.wp, ly.wb, ly.wn, ly.wq, ly.wr);
     NN_HIP(hipGetLastError(), "pack weights");
   }
   return LBM_OK;
@@ -875,10 +1029,11 @@ int nn_forward(lbm_nn n, const float* x, float* yout = nullptr, bool keep_input 
       const int blocks = (n->g.nx / lbmnn::kTX) * (n->g.ny / lbmnn::kTY) * (n->g.nz / lbmnn::kTZ);
       if (direct)
         hipLaunchKernelGGL((lbmnn::conv_pair_kernel<true>), dim3(blocks), dim3(64 * lbmnn::kW), 0, n->stream, nullptr,
-                           x, n->ch[0], n->mean, n->inv_std, ly.wq, b, 1, n->act[l + 1], ly.cout, n->g, n->V);
+                           0, x, n->ch[0], n->mean, n->inv_std, ly.wq, b, 1, nullptr, n->act[l + 1], ly.cout, n->g,
+                           n->V);
       else
         hipLaunchKernelGGL((lbmnn::conv_pair_kernel<false>), dim3(blocks), dim3(64 * lbmnn::kW), 0, n->stream,
-                           n->act[l], nullptr, 0, nullptr, nullptr, ly.wq, b, 1, n->act[l + 1], ly.cout, n->g, n->V);
+                           n->act[l], 16, nullptr, 0, nullptr, nullptr, ly.wq, b, 1, nullptr, n->act[l + 1], ly.cout, n->g, n->V);
       e = hipGetLastError();
     } else if (ly.cinp == 16)
       e = last ? conv<16, true>(n, n->act[l], ly.wp, b, 0, nullptr, yout, ly.cout)
@@ -950,6 +1105,7 @@ int lbm_nn_create(lbm_nn* out, int layers, const int* channels, const int64_t di
   alloc((void**)&n->dA, sizeof(__bf16) * (size_t)V * 32);
   alloc((void**)&n->dB, sizeof(__bf16) * (size_t)V * 32);
   alloc((void**)&n->y, sizeof(float) * (size_t)V * 32);
+  static_assert(lbmnn::kNMaxBlocks * 8 * 32 <= lbmnn::kGMaxBlocks * 1024, "the narrow layer's partials fit as well");
   alloc((void**)&n->part, sizeof(float) * 28 * (size_t)lbmnn::kGMaxBlocks * 1024);
   alloc((void**)&n->lpart, sizeof(double) * (size_t)((V + 255) / 256));
   alloc((void**)&n->loss_acc, sizeof(double));
@@ -957,7 +1113,9 @@ int lbm_nn_create(lbm_nn* out, int layers, const int* channels, const int64_t di
   for (int l = 0; l < layers; ++l) {
     Layer& ly = n->layers[l];
     alloc((void**)&ly.wp, sizeof(__bf16) * 27 * ly.cinp * 32);
-    alloc((void**)&ly.wb, sizeof(__bf16) * 27 * 32 * 32);
+    const bool narrow = l > 0 && l == layers - 1 && ly.cout <= 8;
+    if (narrow) alloc((void**)&ly.wr, sizeof(__bf16) * 14 * 32 * 16);
+    else if (l > 0) alloc((void**)&ly.wb, sizeof(__bf16) * 27 * 32 * 32);
     if (l == layers - 1 && ly.cinp == 32 && ly.cout <= 16) alloc((void**)&ly.wn, sizeof(__bf16) * 27 * 16 * 32);
     if (l == 0 && layers > 1 && ly.cin <= 8) alloc((void**)&ly.wq, sizeof(__bf16) * 14 * 32 * 16);
   }
@@ -1002,6 +1160,7 @@ int lbm_nn_destroy(lbm_nn n) {
     if (ly.wb) (void)hipFree(ly.wb);
     if (ly.wn) (void)hipFree(ly.wn);
     if (ly.wq) (void)hipFree(ly.wq);
+    if (ly.wr) (void)hipFree(ly.wr);
   }
   delete n;
   return LBM_OK;
@@ -1111,18 +1270,23 @@ int lbm_nn_loss_backward(lbm_nn n, const float* x, const float* target, double* 
   if ((rc = nn_forward(n, x))) return rc;
   const int V = n->V, C = n->ch[n->L];
   const int lblocks = (V + 255) / 256;
-  hipLaunchKernelGGL(lbmnn::loss_kernel, dim3(lblocks), dim3(256), 0, n->stream, n->y, x, target, n->inv_out_std, C,
-                     n->out_off, V,
-                     n->dA, n->lpart);
+  const bool narrow = n->layers[n->L - 1].wr != nullptr;  // its gradient has 8 channels per node
+  hipLaunchKernelGGL((narrow ? lbmnn::loss_kernel<8> : lbmnn::loss_kernel<32>), dim3(lblocks), dim3(256), 0, n->stream,
+                     n->y, x, target, n->inv_out_std, C, n->out_off, V, n->dA, n->lpart);
   NN_HIP(hipGetLastError(), "loss kernel");
   // dA holds the gradient with respect to the output of layer l (pre-ReLU for l < L-1)
   __bf16 *dcur = n->dA, *dnext = n->dB;
   const int ntiles = (n->g.nx / lbmnn::kGX) * (n->g.ny / lbmnn::kGY) * (n->g.nz / lbmnn::kGZ);
   const int tpb = (ntiles + lbmnn::kGMaxBlocks - 1) / lbmnn::kGMaxBlocks;
   const int nblk = (ntiles + tpb - 1) / tpb;
+  const int tpb_narrow = (ntiles + lbmnn::kNMaxBlocks - 1) / lbmnn::kNMaxBlocks;
+  const int nblk_narrow = (ntiles + tpb_narrow - 1) / tpb_narrow;
   for (int l = n->L - 1; l >= 0; --l) {
     const Layer& ly = n->layers[l];
-    if (ly.cinp == 16)
+    if (ly.wr)
+      hipLaunchKernelGGL(lbmnn::wgrad_narrow_kernel, dim3(nblk_narrow), dim3(512), 0, n->stream, n->act[l], dcur,
+                         n->part, n->g, ntiles, tpb_narrow, ly.cin, ly.cout);
+    else if (ly.cinp == 16)
       hipLaunchKernelGGL((lbmnn::wgrad_kernel<16>), dim3(nblk), dim3(512), 0, n->stream, n->act[l], dcur, n->part, n->g,
                          ntiles, tpb, ly.cin, ly.cout);
     else
@@ -1130,11 +1294,18 @@ int lbm_nn_loss_backward(lbm_nn n, const float* x, const float* target, double* 
                          ntiles, tpb, ly.cin, ly.cout);
     NN_HIP(hipGetLastError(), "weight gradient kernel");
     hipLaunchKernelGGL(lbmnn::wgrad_sum_kernel, dim3((ly.cin * ly.cout + 63) / 64, 28), dim3(64 * lbmnn::kGRuns), 0,
-                       n->stream, n->part, nblk, ly.cin, ly.cout, n->grads + ly.w_off, n->grads + ly.b_off);
+                       n->stream, n->part, ly.wr ? nblk_narrow : nblk, ly.cin, ly.cout, n->grads + ly.w_off, n->grads + ly.b_off);
     NN_HIP(hipGetLastError(), "weight gradient sums");
     if (l > 0) {
       // gradient with respect to this layer's input = previous output; times the ReLU derivative
-      NN_HIP((conv<32, false>(n, dcur, ly.wb, nullptr, 0, n->act[l], dnext, 32)), "conv backward-data");
+      if (ly.wr) {
+        const int blocks = (n->g.nx / lbmnn::kTX) * (n->g.ny / lbmnn::kTY) * (n->g.nz / lbmnn::kTZ);
+        hipLaunchKernelGGL((lbmnn::conv_pair_kernel<false>), dim3(blocks), dim3(64 * lbmnn::kW), 0, n->stream, dcur, 8,
+                           nullptr, 0, nullptr, nullptr, ly.wr, nullptr, 0, n->act[l], dnext, 32, n->g, V);
+        NN_HIP(hipGetLastError(), "conv backward-data");
+      } else {
+        NN_HIP((conv<32, false>(n, dcur, ly.wb, nullptr, 0, n->act[l], dnext, 32)), "conv backward-data");
+      }
       __bf16* t = dcur;
       dcur = dnext;
       dnext = t;

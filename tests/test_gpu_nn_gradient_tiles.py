@@ -1,6 +1,7 @@
 """Weight gradients where the tiles are dealt out over the work-groups
 differently: fewer tiles than work-groups (one half idle), two and three tiles
-per work-group with a last work-group that has fewer, and both input widths."""
+per work-group with a last work-group that has fewer, both input widths, and
+output layers on both sides of the eight channels that go eight to a node."""
 import numpy as np
 import pytest
 
@@ -9,7 +10,7 @@ from oracle import convnet as N
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("channels", [[5, 32, 3], [16, 32, 16]])
+@pytest.mark.parametrize("channels", [[5, 32, 3], [16, 32, 16], [5, 32, 32, 1], [8, 32, 8], [9, 32, 9]])
 @pytest.mark.parametrize("dims", [(32, 4, 4), (64, 12, 8), (32, 20, 104), (32, 44, 100)])
 def test_gradients(dims, channels):
     import torch
