@@ -770,21 +770,68 @@ __global__ void __launch_bounds__(512) wgrad_narrow_kernel(const __bf16* __restr
 }
 
 // grad[t][i][o] += sum_b part[t][b][i][o] (t < 27) and grad_b[o] += sum_b
-// part[27][b][0][o], part laid out [28][nblk][cin][cout].  A work-group takes 64
-// consecutive (i, o) of one slot; its wavefront s adds the s-th of sixteen equal
-// runs of b, eight loads in flight, and the runs are added in order: a fixed
-// summation order.  One launch: 64^3, 32 channels 5.3 us (7.3 + 4.7 us as two).
+// part[27][b][0][o] of up to kSumLayers layers, part laid out
+// [28][nblk][cin][cout].  A work-group takes 64 consecutive (i, o) of one slot; its
+// wavefront s adds the s-th of sixteen equal runs of b, eight loads in flight,
+// and the runs are added in order: a fixed summation order.  The work-group past
+// the layers' adds a sample's loss to the running sum, where there is one.
+// One launch for a sample's layers: 64^3, 5-32-32-32-3 channels 13.8 us (four
+// launches of 5.3 us and one of 5 for the loss, and the gaps between them).
 constexpr int kGRuns = 16;
-__global__ void __launch_bounds__(64 * kGRuns) wgrad_sum_kernel(const float* __restrict__ part, int nblk, int cin,
-                                                                int cout, float* __restrict__ grad,
-                                                                float* __restrict__ grad_b) {
-  __shared__ float red[kGRuns][64];
+constexpr int kSumLayers = 8;
+
+struct SumLayer {
+  const float* part;
+  float *grad, *grad_b;
+  int nblk, cin, cout;
+  int first;  // its first work-group
+};
+
+struct SumTable {
+  SumLayer layer[kSumLayers];
+  int layers = 0, blocks = 0;      // layers in use, their work-groups
+  const double* lpart = nullptr;   // loss partials (NULL: none)
+  int lcount = 0;
+  double lscale = 0.0;
+  double* loss = nullptr;
+};
+
+// acc[0] += scale * (sum of partial[0 .. n-1]) in a fixed order: the loss of one
+// sample added to a device-side running sum, by the first 256 threads.
+__device__ inline void loss_accumulate(const double* __restrict__ partial, int n, double scale,
+                                       double* __restrict__ acc, double* red) {
+  const int t = threadIdx.x;
+  if (t < 256) {
+    double s = 0.0;
+    for (int i = t; i < n; i += 256) s += partial[i];
+    red[t] = s;
+  }
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (t < w) red[t] += red[t + w];
+    __syncthreads();
+  }
+  if (t == 0) acc[0] += scale * red[0];
+}
+
+__global__ void __launch_bounds__(64 * kGRuns) wgrad_sum_kernel(const SumTable tab) {
+  __shared__ double shared[kGRuns * 64 / 2];
+  if ((int)blockIdx.x >= tab.blocks) {
+    loss_accumulate(tab.lpart, tab.lcount, tab.lscale, tab.loss, shared);
+    return;
+  }
+  float(*red)[64] = reinterpret_cast<float(*)[64]>(shared);
+  int l = 0;
+  while (l + 1 < tab.layers && (int)blockIdx.x >= tab.layer[l + 1].first) ++l;
+  const SumLayer& ly = tab.layer[l];
+  const int cio = ly.cin * ly.cout, per_slot = (cio + 63) / 64, nblk = ly.nblk;
+  const int t = ((int)blockIdx.x - ly.first) / per_slot;
   const int lane = threadIdx.x & 63, s = threadIdx.x >> 6;
-  const int cio = cin * cout, t = blockIdx.y, io = blockIdx.x * 64 + lane;
+  const int io = ((int)blockIdx.x - ly.first - t * per_slot) * 64 + lane;
   const int b0 = nblk * s / kGRuns, b1 = nblk * (s + 1) / kGRuns;
   float acc = 0.f;
   if (io < cio) {
-    const float* src = part + ((size_t)t * nblk + b0) * cio + io;
+    const float* src = ly.part + ((size_t)t * nblk + b0) * cio + io;
     int b = b0;
     for (; b + 8 <= b1; b += 8, src += (size_t)8 * cio) {
       float v[8];
@@ -797,11 +844,11 @@ __global__ void __launch_bounds__(64 * kGRuns) wgrad_sum_kernel(const float* __r
   }
   red[s][lane] = acc;
   __syncthreads();
-  if (s || io >= cio || (t == 27 && io >= cout)) return;
+  if (s || io >= cio || (t == 27 && io >= ly.cout)) return;
 #pragma unroll
   for (int k = 1; k < kGRuns; ++k) acc += red[k][lane];
-  if (t < 27) grad[(size_t)t * cio + io] += acc;
-  else grad_b[io] += acc;
+  if (t < 27) ly.grad[(size_t)t * cio + io] += acc;
+  else ly.grad_b[io] += acc;
 }
 
 // r_c = y_c + (x_f - target_f) / out_std_c with f = off + c; loss partial sums
@@ -838,22 +885,6 @@ __global__ void __launch_bounds__(256) loss_kernel(const float* __restrict__ y, 
     __syncthreads();
   }
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
-}
-
-// acc[0] += scale * (sum of partial[0 .. n-1]) in a fixed order (one
-// work-group): the loss of one sample added to a device-side running sum.
-__global__ void __launch_bounds__(256) loss_accumulate_kernel(const double* __restrict__ partial, int n, double scale,
-                                                              double* __restrict__ acc) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) s += partial[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) acc[0] += scale * red[0];
 }
 
 __global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ p, const float* __restrict__ g,
@@ -965,6 +996,7 @@ struct lbm_nn_ctx {
   __bf16 *dA = nullptr, *dB = nullptr;  // gradient ping-pong, bf16 [V][32]
   float* y = nullptr;                   // network output planes [c_L][V]
   float* part = nullptr;                // weight-gradient partials, per work-group
+  size_t part_size = 0;                 // floats of it
   int out_off = 0;                      // output c corrects / is compared with field out_off + c
   double limit = 0.0;                   // lbm_nn_correct clips outputs to [-limit, limit] (0: no clip)
   double* lpart = nullptr;              // loss partials
@@ -991,6 +1023,16 @@ int nn_pack_weights(lbm_nn n) {
     NN_HIP(hipGetLastError(), "pack weights");
   }
   return LBM_OK;
+}
+
+// An output layer whose gradient is kept as 8 channels per node.
+bool narrow_output(const lbm_nn_ctx& n, int l) { return l > 0 && l == n.L - 1 && n.layers[l].cout <= 8; }
+
+// Work-groups of a weight gradient, and the tiles each of them takes.
+void gradient_blocks(const lbmnn::Grid& g, int& ntiles, int& tpb, int& nblk, int most) {
+  ntiles = (g.nx / lbmnn::kGX) * (g.ny / lbmnn::kGY) * (g.nz / lbmnn::kGZ);
+  tpb = (ntiles + most - 1) / most;
+  nblk = (ntiles + tpb - 1) / tpb;
 }
 
 template <int CIN, bool PLANAR>
@@ -1105,16 +1147,23 @@ int lbm_nn_create(lbm_nn* out, int layers, const int* channels, const int64_t di
   alloc((void**)&n->dA, sizeof(__bf16) * (size_t)V * 32);
   alloc((void**)&n->dB, sizeof(__bf16) * (size_t)V * 32);
   alloc((void**)&n->y, sizeof(float) * (size_t)V * 32);
-  static_assert(lbmnn::kNMaxBlocks * 8 * 32 <= lbmnn::kGMaxBlocks * 1024, "the narrow layer's partials fit as well");
-  alloc((void**)&n->part, sizeof(float) * 28 * (size_t)lbmnn::kGMaxBlocks * 1024);
+  // The partials of all layers, so that one launch adds them up, or of four wide ones at the most.
+  static_assert(lbmnn::kNMaxBlocks * 8 * 32 <= lbmnn::kGMaxBlocks * 1024, "a narrow layer's are no more than a wide one's");
+  for (int l = 0; l < layers; ++l) {
+    const Layer& ly = n->layers[l];
+    int ntiles, tpb, nblk;
+    gradient_blocks(n->g, ntiles, tpb, nblk, narrow_output(*n, l) ? lbmnn::kNMaxBlocks : lbmnn::kGMaxBlocks);
+    n->part_size += (size_t)28 * nblk * ly.cin * ly.cout;
+  }
+  n->part_size = std::min(n->part_size, (size_t)4 * 28 * lbmnn::kGMaxBlocks * 1024);
+  alloc((void**)&n->part, sizeof(float) * n->part_size);
   alloc((void**)&n->lpart, sizeof(double) * (size_t)((V + 255) / 256));
   alloc((void**)&n->loss_acc, sizeof(double));
   alloc((void**)&n->fld, sizeof(float) * 16 * (size_t)V);
   for (int l = 0; l < layers; ++l) {
     Layer& ly = n->layers[l];
     alloc((void**)&ly.wp, sizeof(__bf16) * 27 * ly.cinp * 32);
-    const bool narrow = l > 0 && l == layers - 1 && ly.cout <= 8;
-    if (narrow) alloc((void**)&ly.wr, sizeof(__bf16) * 14 * 32 * 16);
+    if (narrow_output(*n, l)) alloc((void**)&ly.wr, sizeof(__bf16) * 14 * 32 * 16);
     else if (l > 0) alloc((void**)&ly.wb, sizeof(__bf16) * 27 * 32 * 32);
     if (l == layers - 1 && ly.cinp == 32 && ly.cout <= 16) alloc((void**)&ly.wn, sizeof(__bf16) * 27 * 16 * 32);
     if (l == 0 && layers > 1 && ly.cin <= 8) alloc((void**)&ly.wq, sizeof(__bf16) * 14 * 32 * 16);
@@ -1276,31 +1325,42 @@ int lbm_nn_loss_backward(lbm_nn n, const float* x, const float* target, double* 
   NN_HIP(hipGetLastError(), "loss kernel");
   // dA holds the gradient with respect to the output of layer l (pre-ReLU for l < L-1)
   __bf16 *dcur = n->dA, *dnext = n->dB;
-  const int ntiles = (n->g.nx / lbmnn::kGX) * (n->g.ny / lbmnn::kGY) * (n->g.nz / lbmnn::kGZ);
-  const int tpb = (ntiles + lbmnn::kGMaxBlocks - 1) / lbmnn::kGMaxBlocks;
-  const int nblk = (ntiles + tpb - 1) / tpb;
-  const int tpb_narrow = (ntiles + lbmnn::kNMaxBlocks - 1) / lbmnn::kNMaxBlocks;
-  const int nblk_narrow = (ntiles + tpb_narrow - 1) / tpb_narrow;
+  int ntiles, tpb, tpb_narrow, nblk, nblk_narrow;
+  gradient_blocks(n->g, ntiles, tpb, nblk, lbmnn::kGMaxBlocks);
+  gradient_blocks(n->g, ntiles, tpb_narrow, nblk_narrow, lbmnn::kNMaxBlocks);
+  lbmnn::SumTable sums;
+  size_t used = 0;  // floats of the partials that wait for their sum
+  auto add_up = [&]() {
+    const unsigned blocks = (unsigned)(sums.blocks + (sums.lpart ? 1 : 0));
+    hipLaunchKernelGGL(lbmnn::wgrad_sum_kernel, dim3(blocks), dim3(64 * lbmnn::kGRuns), 0, n->stream, sums);
+    sums = lbmnn::SumTable();
+    used = 0;
+    return hipGetLastError();
+  };
   for (int l = n->L - 1; l >= 0; --l) {
     const Layer& ly = n->layers[l];
+    const int blocks = ly.wr ? nblk_narrow : nblk;
+    const size_t need = (size_t)28 * blocks * ly.cin * ly.cout;
+    if (sums.layers == lbmnn::kSumLayers || used + need > n->part_size) NN_HIP(add_up(), "weight gradient sums");
+    float* part = n->part + used;
+    used += need;
     if (ly.wr)
-      hipLaunchKernelGGL(lbmnn::wgrad_narrow_kernel, dim3(nblk_narrow), dim3(512), 0, n->stream, n->act[l], dcur,
-                         n->part, n->g, ntiles, tpb_narrow, ly.cin, ly.cout);
+      hipLaunchKernelGGL(lbmnn::wgrad_narrow_kernel, dim3(blocks), dim3(512), 0, n->stream, n->act[l], dcur, part,
+                         n->g, ntiles, tpb_narrow, ly.cin, ly.cout);
     else if (ly.cinp == 16)
-      hipLaunchKernelGGL((lbmnn::wgrad_kernel<16>), dim3(nblk), dim3(512), 0, n->stream, n->act[l], dcur, n->part, n->g,
+      hipLaunchKernelGGL((lbmnn::wgrad_kernel<16>), dim3(blocks), dim3(512), 0, n->stream, n->act[l], dcur, part, n->g,
                          ntiles, tpb, ly.cin, ly.cout);
     else
-      hipLaunchKernelGGL((lbmnn::wgrad_kernel<32>), dim3(nblk), dim3(512), 0, n->stream, n->act[l], dcur, n->part, n->g,
+      hipLaunchKernelGGL((lbmnn::wgrad_kernel<32>), dim3(blocks), dim3(512), 0, n->stream, n->act[l], dcur, part, n->g,
                          ntiles, tpb, ly.cin, ly.cout);
     NN_HIP(hipGetLastError(), "weight gradient kernel");
-    hipLaunchKernelGGL(lbmnn::wgrad_sum_kernel, dim3((ly.cin * ly.cout + 63) / 64, 28), dim3(64 * lbmnn::kGRuns), 0,
-                       n->stream, n->part, ly.wr ? nblk_narrow : nblk, ly.cin, ly.cout, n->grads + ly.w_off, n->grads + ly.b_off);
-    NN_HIP(hipGetLastError(), "weight gradient sums");
+    sums.layer[sums.layers++] = {part, n->grads + ly.w_off, n->grads + ly.b_off, blocks, ly.cin, ly.cout, sums.blocks};
+    sums.blocks += (ly.cin * ly.cout + 63) / 64 * 28;
     if (l > 0) {
       // gradient with respect to this layer's input = previous output; times the ReLU derivative
       if (ly.wr) {
-        const int blocks = (n->g.nx / lbmnn::kTX) * (n->g.ny / lbmnn::kTY) * (n->g.nz / lbmnn::kTZ);
-        hipLaunchKernelGGL((lbmnn::conv_pair_kernel<false>), dim3(blocks), dim3(64 * lbmnn::kW), 0, n->stream, dcur, 8,
+        const int tiles = (n->g.nx / lbmnn::kTX) * (n->g.ny / lbmnn::kTY) * (n->g.nz / lbmnn::kTZ);
+        hipLaunchKernelGGL((lbmnn::conv_pair_kernel<false>), dim3(tiles), dim3(64 * lbmnn::kW), 0, n->stream, dcur, 8,
                            nullptr, 0, nullptr, nullptr, ly.wr, nullptr, 0, n->act[l], dnext, 32, n->g, V);
         NN_HIP(hipGetLastError(), "conv backward-data");
       } else {
@@ -1311,6 +1371,13 @@ int lbm_nn_loss_backward(lbm_nn n, const float* x, const float* target, double* 
       dnext = t;
     }
   }
+  if (!loss) {
+    sums.lpart = n->lpart;
+    sums.lcount = lblocks;
+    sums.lscale = 1.0 / ((double)C * V);
+    sums.loss = n->loss_acc;
+  }
+  NN_HIP(add_up(), "weight gradient sums");
   if (loss) {
     std::vector<double> h(lblocks);
     NN_HIP(hipMemcpyAsync(h.data(), n->lpart, sizeof(double) * lblocks, hipMemcpyDeviceToHost, n->stream),
@@ -1320,9 +1387,6 @@ int lbm_nn_loss_backward(lbm_nn n, const float* x, const float* target, double* 
     for (double x2 : h) s += x2;
     *loss = s / ((double)C * V);
   } else {
-    hipLaunchKernelGGL(lbmnn::loss_accumulate_kernel, dim3(1), dim3(256), 0, n->stream, n->lpart, lblocks,
-                       1.0 / ((double)C * V), n->loss_acc);
-    NN_HIP(hipGetLastError(), "loss accumulation");
     ++n->loss_count;
   }
   return LBM_OK;
