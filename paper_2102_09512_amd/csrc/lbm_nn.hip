@@ -21,6 +21,7 @@
 // gradient (n = output channel), summed over nodes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -907,10 +908,27 @@ __global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ p, const 
 // (16 padded outputs, 32 padded inputs); for an input layer of at most 8
 // channels, wq[p][o][k] (taps 2p and 2p + 1, 8 channels each); for an output
 // layer of at most 8, wr[p][i][k] the same of the mirrored convolution
-__global__ void __launch_bounds__(256) pack_weights_kernel(const float* __restrict__ W, int cin, int cout, int cinp,
-                                                           __bf16* __restrict__ wp, __bf16* __restrict__ wb,
-                                                           __bf16* __restrict__ wn, __bf16* __restrict__ wq,
-                                                           __bf16* __restrict__ wr) {
+//
+// One launch (grid y = layer) packs up to kPackLayers layers: 4.4 us for four (four
+// launches of 3.8 us, and the gaps between them).
+constexpr int kPackLayers = 8;
+
+struct PackLayer {
+  const float* W;
+  int cin, cout, cinp;
+  __bf16 *wp, *wb, *wn, *wq, *wr;
+};
+
+struct PackTable {
+  PackLayer layer[kPackLayers];
+};
+
+__global__ void __launch_bounds__(256) pack_weights_kernel(const PackTable tab) {
+  const PackLayer& ly = tab.layer[blockIdx.y];
+  const float* __restrict__ W = ly.W;
+  const int cin = ly.cin, cout = ly.cout, cinp = ly.cinp;
+  __bf16 *__restrict__ wp = ly.wp, *__restrict__ wb = ly.wb, *__restrict__ wn = ly.wn, *__restrict__ wq = ly.wq,
+         *__restrict__ wr = ly.wr;
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e < 27 * cinp * 32) {  // wp element (t, cc, o, k)
     const int k = e % 16, o = (e / 16) % 32, cc = (e / 512) % (cinp / 16), t = e / (512 * (cinp / 16));
@@ -1015,11 +1033,14 @@ int nn_select(lbm_nn n) {
 }
 
 int nn_pack_weights(lbm_nn n) {
-  for (int l = 0; l < n->L; ++l) {
-    Layer& ly = n->layers[l];
-    const int total = 27 * 32 * 32 > 27 * ly.cinp * 32 ? 27 * 32 * 32 : 27 * ly.cinp * 32;
-    hipLaunchKernelGGL(lbmnn::pack_weights_kernel, dim3((total + 255) / 256), dim3(256), 0, n->stream,
-                       n->params + ly.w_off, ly.cin, ly.cout, ly.cinp, ly.wp, ly.wb, ly.wn, ly.wq, ly.wr);
+  for (int first = 0; first < n->L; first += lbmnn::kPackLayers) {
+    const int count = std::min(n->L - first, lbmnn::kPackLayers);
+    lbmnn::PackTable tab{};
+    for (int k = 0; k < count; ++k) {
+      const Layer& ly = n->layers[first + k];
+      tab.layer[k] = {n->params + ly.w_off, ly.cin, ly.cout, ly.cinp, ly.wp, ly.wb, ly.wn, ly.wq, ly.wr};
+    }
+    hipLaunchKernelGGL(lbmnn::pack_weights_kernel, dim3(27 * 32 * 32 / 256, count), dim3(256), 0, n->stream, tab);
     NN_HIP(hipGetLastError(), "pack weights");
   }
   return LBM_OK;
