@@ -633,27 +633,33 @@ __global__ void __launch_bounds__(512) wgrad_kernel(const __bf16* __restrict__ i
   }
 }
 
-// The same partials for an output layer of at most 8 channels (dout bf16
-// [v][8], in [v][32]).  The product is turned round: the 32 rows are the input
-// channels of the tile's own nodes u, and the 32 columns are four taps times 8
-// output channels at u - s_t, so that nine columns' worth of (dy, dz) pairs
-// per dx take three products where a tap at a time takes nine, the input needs
-// no halo and the output gradient's is four times smaller.  Waves 0 to 2 of a
-// half own dx = -1, 0, 1; wave 3 owns the bias (a product with ones).
-// 64^3, 32 to 3 channels: 15.5 us (17.9 with one work-group per compute unit;
-// 27.4 in wgrad_kernel).  Two work-groups fit a compute unit, and the partials
-// of so few channels cost little.
+// The same partials for a layer with at most 8 channels on one side: an output
+// layer (IN false; wide: the input, narrow: dout, 8 channels per node) or an input
+// layer (IN true; wide: dout, narrow: the input, the first 8 of `stride` channels
+// per node).  The product is turned round: the 32 rows are the channels of the
+// wide side at the tile's own nodes u, and the 32 columns are four taps times 8
+// channels of the narrow side at u - s_t (u + s_t for an input layer), so that
+// nine columns' worth of (dy, dz) pairs per dx take three products where a tap at a
+// time takes nine, the wide side needs no halo and the narrow side is four times
+// smaller.  Waves 0 to 2 of a half own dx = -1, 0, 1; wave 3 owns the bias (a
+// product with ones).
+// 64^3: 32 to 3 channels 15.5 us (17.9 with one work-group per compute unit; 27.4
+// in wgrad_kernel); 5 to 32 channels 19.0 us on a card 4% slower (23.4 in
+// wgrad_kernel).  Two work-groups fit a compute unit, and the partials of so few
+// channels cost little.
 constexpr int kNMaxBlocks = 512;
 
-__global__ void __launch_bounds__(512) wgrad_narrow_kernel(const __bf16* __restrict__ in,
-                                                           const __bf16* __restrict__ dout, float* __restrict__ part,
-                                                           const Grid g, int ntiles, int tpb, int cin, int cout) {
+template <bool IN>
+__global__ void __launch_bounds__(512, 4) wgrad_narrow_kernel(const __bf16* __restrict__ wide,
+                                                           const __bf16* __restrict__ narrow, int stride,
+                                                           float* __restrict__ part, const Grid g, int ntiles, int tpb,
+                                                           int cin, int cout) {
   constexpr int kHalf = 32 * kGPlaneD + 8 * kGPlaneIn;  // bf16 elements of one half's tile
   static_assert(4 * 3 * 16 * 64 * sizeof(float) <= 2 * kHalf * sizeof(__bf16), "the halves' sums fit the tiles' LDS");
   __shared__ __attribute__((aligned(16))) __bf16 lds[2 * kHalf];
   const int half_wg = threadIdx.x >> 8, t = threadIdx.x & 255;
-  __bf16* inT = lds + half_wg * kHalf;
-  __bf16* dT = inT + 32 * kGPlaneD;
+  __bf16* wT = lds + half_wg * kHalf;
+  __bf16* nT = wT + 32 * kGPlaneD;
   const int lane = t & 63, w = t >> 6;
   const int r = lane & 31, half = lane >> 5;
   const int tx = g.nx / kGX, ty = g.ny / kGY;
@@ -664,30 +670,30 @@ __global__ void __launch_bounds__(512) wgrad_narrow_kernel(const __bf16* __restr
   const int bl = xcd_tile(blockIdx.x, gridDim.x);
   const int first = bl * tpb, last = min(first + tpb, ntiles);
   // items of two x neighbours times 8 channels
-  constexpr int NIN = (kGX / 2) * kGY * kGZ * 4, NITI = NIN / 256;
-  constexpr int ND = (kGHX / 2) * kGHY * kGHZ, NITD = (ND + 255) / 256;
-  static_assert(NIN % 256 == 0 && kGHX % 2 == 0, "whole items");
-  u4 si[NITI][2], sd[NITD][2];
+  constexpr int NW = (kGX / 2) * kGY * kGZ * 4, NITW = NW / 256;
+  constexpr int NN = (kGHX / 2) * kGHY * kGHZ, NITN = (NN + 255) / 256;
+  static_assert(NW % 256 == 0 && kGHX % 2 == 0, "whole items");
+  u4 sw[NITW][2], sn[NITN][2];
   auto request = [&](int tile) {
     const int x0 = (tile % tx) * kGX, y0 = ((tile / tx) % ty) * kGY, z0 = (tile / (tx * ty)) * kGZ;
 #pragma unroll
-    for (int k = 0; k < NITI; ++k) {
+    for (int k = 0; k < NITW; ++k) {
       const int e = t + k * 256;
       const int pair = e % (kGX / 2), c8 = (e / (kGX / 2)) % 4, row = e / (kGX / 2 * 4);
       const __bf16* base =
-          in + ((size_t)(x0 + 2 * pair) + (size_t)g.nx * (y0 + row % kGY + g.ny * (z0 + row / kGY))) * 32 + 8 * c8;
+          wide + ((size_t)(x0 + 2 * pair) + (size_t)g.nx * (y0 + row % kGY + g.ny * (z0 + row / kGY))) * 32 + 8 * c8;
 #pragma unroll
-      for (int q = 0; q < 2; ++q) si[k][q] = *(const u4*)(base + q * 32);
+      for (int q = 0; q < 2; ++q) sw[k][q] = *(const u4*)(base + q * 32);
     }
 #pragma unroll
-    for (int k = 0; k < NITD; ++k) {
+    for (int k = 0; k < NITN; ++k) {
       const int e = t + k * 256;
-      if (e < ND) {
+      if (e < NN) {
         const int pair = e % (kGHX / 2), row = e / (kGHX / 2);
         const int gy = wrap(y0 + row % kGHY - 1, g.ny), gz = wrap(z0 + row / kGHY - 1, g.nz);
-        const __bf16* base = dout + (size_t)(g.nx * (gy + g.ny * gz)) * 8;
+        const __bf16* base = narrow + (size_t)(g.nx * (gy + g.ny * gz)) * stride;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) sd[k][q] = *(const u4*)(base + (size_t)wrap(x0 + 2 * pair + q - 1, g.nx) * 8);
+        for (int q = 0; q < 2; ++q) sn[k][q] = *(const u4*)(base + (size_t)wrap(x0 + 2 * pair + q - 1, g.nx) * stride);
       }
     }
   };
@@ -698,15 +704,15 @@ __global__ void __launch_bounds__(512) wgrad_narrow_kernel(const __bf16* __restr
     __syncthreads();  // every wave is done with the previous tiles
     if (active) {
 #pragma unroll
-      for (int k = 0; k < NITI; ++k) {
+      for (int k = 0; k < NITW; ++k) {
         const int e = t + k * 256;
         const int pair = e % (kGX / 2), c8 = (e / (kGX / 2)) % 4, row = e / (kGX / 2 * 4);
-        transpose(si[k], inT + 8 * c8 * kGPlaneD + row * kGX + 2 * pair, kGPlaneD);
+        transpose(sw[k], wT + 8 * c8 * kGPlaneD + row * kGX + 2 * pair, kGPlaneD);
       }
 #pragma unroll
-      for (int k = 0; k < NITD; ++k) {
+      for (int k = 0; k < NITN; ++k) {
         const int e = t + k * 256;
-        if (e < ND) transpose(sd[k], dT + e / (kGHX / 2) * kGRow + 2 * (e % (kGHX / 2)), kGPlaneIn);
+        if (e < NN) transpose(sn[k], nT + e / (kGHX / 2) * kGRow + 2 * (e % (kGHX / 2)), kGPlaneIn);
       }
     }
     __syncthreads();
@@ -717,19 +723,22 @@ __global__ void __launch_bounds__(512) wgrad_narrow_kernel(const __bf16* __restr
       const int yy = row % kGY, zz = row / kGY;
 #pragma unroll
       for (int kb = 0; kb < kGX; kb += 16) {
-        auto column = [&](int pair, int shift) {  // output channel r % 8 at u - s of these nodes
-          const int dy = pair % 3 - 1, dz = pair / 3 - 1;
+        auto column = [&](int pair, int shift) {  // narrow channel r % 8 at u -+ s of these nodes
+          const int dy = IN ? pair % 3 - 1 : 1 - pair % 3, dz = IN ? pair / 3 - 1 : 1 - pair / 3;
           const __bf16* src =
-              dT + (r & 7) * kGPlaneIn + ((zz - dz + 1) * kGHY + yy - dy + 1) * kGRow + kb + 8 * half;
+              nT + (r & 7) * kGPlaneIn + ((zz + dz + 1) * kGHY + yy + dy + 1) * kGRow + kb + 8 * half;
           return shifted(*(const u4*)src, *(const u4*)(src + 8), shift);
         };
+        bf8 a = ones;
+        if (w < 3 || IN) a = *(const bf8*)(wT + r * kGPlaneD + row * kGX + kb + 8 * half);
         if (w < 3) {
-          const bf8 a = *(const bf8*)(inT + r * kGPlaneD + row * kGX + kb + 8 * half);
 #pragma unroll
           for (int j = 0; j < 3; ++j)
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, column(min(4 * j + (r >> 3), 8), 2 - w), acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, column(min(4 * j + (r >> 3), 8), IN ? w : 2 - w), acc[j],
+                                                             0, 0, 0);
         } else {
-          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, column(4, 1), acc[0], 0, 0, 0);
+          const bf8 b = IN ? ones : column(4, 1);
+          acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[0], 0, 0, 0);
         }
       }
     }
@@ -754,18 +763,19 @@ __global__ void __launch_bounds__(512) wgrad_narrow_kernel(const __bf16* __restr
   }
   if (half_wg) return;
   // accumulator i of lane l holds row m = 8(i/4) + 4(l/32) + i%4, column r = l%32
-  const int o = r & 7;
+  const int c = r & 7;  // narrow channel
+  const int cw = IN ? cout : cin, cn = IN ? cin : cout;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const int pair = 4 * k + (r >> 3);
     const bool bias = w == 3 && k == 0 && r < 8;
-    if (o >= cout || !(bias || (w < 3 && pair < 9))) continue;
+    if (c >= cn || !(bias || (w < 3 && pair < 9))) continue;
     const int slot = w == 3 ? 27 : 3 * pair + w;
     float* dst = part + ((size_t)slot * gridDim.x + bl) * cin * cout;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int m = 8 * (i >> 2) + 4 * half + (i & 3);
-      if (m < cin) dst[m * cout + o] = acc[k][i];
+      if (m < cw) dst[IN ? c * cout + m : m * cout + c] = acc[k][i];
     }
   }
 }
@@ -1049,6 +1059,12 @@ int nn_pack_weights(lbm_nn n) {
 // An output layer whose gradient is kept as 8 channels per node.
 bool narrow_output(const lbm_nn_ctx& n, int l) { return l > 0 && l == n.L - 1 && n.layers[l].cout <= 8; }
 
+// A layer with at most 8 channels on one side and 32 on the other, or an output
+// layer of them.
+bool narrow_side(const lbm_nn_ctx& n, int l) {
+  return narrow_output(n, l) || (l == 0 && n.L > 1 && n.layers[l].cin <= 8);
+}
+
 // Work-groups of a weight gradient, and the tiles each of them takes.
 void gradient_blocks(const lbmnn::Grid& g, int& ntiles, int& tpb, int& nblk, int most) {
   ntiles = (g.nx / lbmnn::kGX) * (g.ny / lbmnn::kGY) * (g.nz / lbmnn::kGZ);
@@ -1173,7 +1189,7 @@ int lbm_nn_create(lbm_nn* out, int layers, const int* channels, const int64_t di
   for (int l = 0; l < layers; ++l) {
     const Layer& ly = n->layers[l];
     int ntiles, tpb, nblk;
-    gradient_blocks(n->g, ntiles, tpb, nblk, narrow_output(*n, l) ? lbmnn::kNMaxBlocks : lbmnn::kGMaxBlocks);
+    gradient_blocks(n->g, ntiles, tpb, nblk, narrow_side(*n, l) ? lbmnn::kNMaxBlocks : lbmnn::kGMaxBlocks);
     n->part_size += (size_t)28 * nblk * ly.cin * ly.cout;
   }
   n->part_size = std::min(n->part_size, (size_t)4 * 28 * lbmnn::kGMaxBlocks * 1024);
@@ -1360,14 +1376,18 @@ int lbm_nn_loss_backward(lbm_nn n, const float* x, const float* target, double* 
   };
   for (int l = n->L - 1; l >= 0; --l) {
     const Layer& ly = n->layers[l];
-    const int blocks = ly.wr ? nblk_narrow : nblk;
+    const bool thin = narrow_side(*n, l);
+    const int blocks = thin ? nblk_narrow : nblk;
     const size_t need = (size_t)28 * blocks * ly.cin * ly.cout;
     if (sums.layers == lbmnn::kSumLayers || used + need > n->part_size) NN_HIP(add_up(), "weight gradient sums");
     float* part = n->part + used;
     used += need;
     if (ly.wr)
-      hipLaunchKernelGGL(lbmnn::wgrad_narrow_kernel, dim3(blocks), dim3(512), 0, n->stream, n->act[l], dcur, part,
-                         n->g, ntiles, tpb_narrow, ly.cin, ly.cout);
+      hipLaunchKernelGGL((lbmnn::wgrad_narrow_kernel<false>), dim3(blocks), dim3(512), 0, n->stream, n->act[l], dcur, 8,
+                         part, n->g, ntiles, tpb_narrow, ly.cin, ly.cout);
+    else if (thin)
+      hipLaunchKernelGGL((lbmnn::wgrad_narrow_kernel<true>), dim3(blocks), dim3(512), 0, n->stream, dcur, n->act[l], 16,
+                         part, n->g, ntiles, tpb_narrow, ly.cin, ly.cout);
     else if (ly.cinp == 16)
       hipLaunchKernelGGL((lbmnn::wgrad_kernel<16>), dim3(blocks), dim3(512), 0, n->stream, n->act[l], dcur, part, n->g,
                          ntiles, tpb, ly.cin, ly.cout);
