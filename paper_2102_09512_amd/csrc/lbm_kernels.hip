@@ -1487,6 +1487,13 @@ struct NodeEq {
   }
 };
 
+// Ends the expressions that the fields come from: a product and a sum on either
+// side of it are not fused, so equal fields give equal equilibria whatever they
+// were computed from.
+__device__ inline void as_values(double& rho, double* u, double& T) {
+  asm("" : "+v"(rho), "+v"(u[0]), "+v"(u[1]), "+v"(u[2]), "+v"(T));
+}
+
 // New fields of a node: the planes rho, u_x, u_y, u_z, T of F ...
 struct NewFields {
   const double* F;
@@ -1526,6 +1533,7 @@ struct Corrected {
 
 // f_i += f^eq_i(new) - f^eq_i(old), g likewise (equilibria evaluated in FP64
 // for either storage), the old fields those of the populations themselves.
+// Where the new fields are the old ones, the populations keep every bit.
 // The populations are read and written once; with two equilibria a node in
 // 2 x 60 registers, FP64 arithmetic and the latency of a few wavefronts bind
 // at the corrector's 64^3: 29.6 us (45.2 us with the old fields from memory and
@@ -1544,11 +1552,14 @@ __global__ void __launch_bounds__(256, 2) fields_add_kernel(S* __restrict__ pops
   double s0, j[3], se, rho, u[3], T, rhoE;
   pair_sums<D>(v, s0, j, &se);
   fields_of<D>(p, s0, j, se, rho, u, T, rhoE);
+  as_values(rho, u, T);
   const NodeEq<D, DEV> before(k, rho, u, T);
   fresh(n, rho, u, T);
+  as_values(rho, u, T);
   const NodeEq<D, DEV> after(k, rho, u, T);
 #pragma unroll
   for (int r = 0; r < Q / 3; ++r) {
+#pragma clang fp contract(off)  // both sides of a difference are rounded
     const auto o = before.row(k, r), w = after.row(k, r);
     const double dA = k.rho0 * (w.dA - o.dA), dV = k.rho0 * (w.V2 - o.V2);  // of the terms with constant factors
 #pragma unroll
