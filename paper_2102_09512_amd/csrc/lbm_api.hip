@@ -52,18 +52,23 @@ int select_device(Ctx* c) {
   return LBM_OK;
 }
 
-// Whether a kernel of handle c may address caller memory p itself: memory of
-// the handle's own device, aligned to its element.  Anything else that a copy
-// accepts (another device's memory, pinned host memory, an odd address) goes
-// through a staging buffer.
-bool direct(const Ctx* c, const void* p, size_t element) {
+// Whether a kernel of handle c may address `bytes` of caller memory at p
+// itself: memory of the handle's own device, aligned to its element, inside one
+// allocation.  Anything else that a copy accepts (another device's memory,
+// pinned host memory, an odd address) goes through a staging buffer, and an
+// array that is too small is refused by the copy, which looks at its allocation.
+bool direct(const Ctx* c, const void* p, size_t element, size_t bytes) {
   if ((uintptr_t)p % element) return false;
   hipPointerAttribute_t a;
-  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return a.type == hipMemoryTypeDevice && a.device == c->device;
+  const size_t offset = (size_t)((uintptr_t)p - (uintptr_t)base);
+  return a.type == hipMemoryTypeDevice && a.device == c->device && offset <= size && bytes <= size - offset;
 }
 
 int ensure_fields(Ctx* c) {
@@ -460,8 +465,10 @@ int lbm_moments(lbm_handle h, double* rho, double* u, double* T, int mem) {
   if (!c->initialised) return fail(LBM_ESTATE, "lbm_moments: call lbm_init_fields first");
   int rc = select_device(c);
   if (rc) return rc;
-  auto straight = [c](const void* q) { return !q || direct(c, q, sizeof(double)); };
-  if (mem == LBM_DEVICE && straight(rho) && straight(u) && straight(T)) {
+  auto straight = [c](const void* q, int planes) {
+    return !q || direct(c, q, sizeof(double), sizeof(double) * (size_t)planes * (size_t)c->N);
+  };
+  if (mem == LBM_DEVICE && straight(rho, 1) && straight(u, c->lattice) && straight(T, 1)) {
     if (rho || u || T)
       HIP_OR_FAIL(lbm::launch_moments(*c, c->buf[c->cur], rho, u, c->lattice, T), "moments kernel");
     return LBM_OK;
@@ -541,7 +548,7 @@ int lbm_get_state(lbm_handle h, void* buf, size_t bytes, int mem) {
   if (bytes != lbm_state_bytes(h)) return fail(LBM_EINVAL, "lbm_get_state: wrong buffer size");
   int rc = select_device(c);
   if (rc) return rc;
-  if (mem == LBM_DEVICE && direct(c, buf, word_of(c->precision))) {
+  if (mem == LBM_DEVICE && direct(c, buf, word_of(c->precision), bytes)) {
     HIP_OR_FAIL(lbm::launch_pack(*c, c->buf[c->cur], buf), "pack kernel");
     return LBM_OK;
   }
@@ -564,7 +571,7 @@ int lbm_set_state(lbm_handle h, const void* buf, size_t bytes, int mem, int64_t 
   int rc = select_device(c);
   if (rc) return rc;
   const void* state = buf;
-  if (mem == LBM_HOST || !direct(c, buf, word_of(c->precision))) {
+  if (mem == LBM_HOST || !direct(c, buf, word_of(c->precision), bytes)) {
     HIP_OR_FAIL(hipMemcpyAsync(c->buf[1], buf, bytes,
                                mem == LBM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, c->stream),
                 "copy state");
