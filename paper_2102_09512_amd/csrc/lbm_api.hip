@@ -473,13 +473,16 @@ int lbm_moments(lbm_handle h, double* rho, double* u, double* T, int mem) {
       HIP_OR_FAIL(lbm::launch_moments(*c, c->buf[c->cur], rho, u, c->lattice, T), "moments kernel");
     return LBM_OK;
   }
-  if ((rc = ensure_fields(c))) return rc;
+  // into the other population buffer (its content is dead between steps, and 2Q
+  // values a node hold the five planes in either storage), then copied out: no
+  // allocation, so the call can be captured
   const int64_t N = c->N;
-  HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], c->fields), "moments kernel");
+  double* fields = static_cast<double*>(c->buf[c->cur ^ 1]);
+  HIP_OR_FAIL(lbm::launch_fields(*c, c->buf[c->cur], fields), "moments kernel");
   const hipMemcpyKind kind = mem == LBM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
-  if (rho) HIP_OR_FAIL(hipMemcpyAsync(rho, c->fields, sizeof(double) * N, kind, c->stream), "copy rho");
-  if (u) HIP_OR_FAIL(hipMemcpyAsync(u, c->fields + N, sizeof(double) * N * c->lattice, kind, c->stream), "copy u");
-  if (T) HIP_OR_FAIL(hipMemcpyAsync(T, c->fields + 4 * N, sizeof(double) * N, kind, c->stream), "copy T");
+  if (rho) HIP_OR_FAIL(hipMemcpyAsync(rho, fields, sizeof(double) * N, kind, c->stream), "copy rho");
+  if (u) HIP_OR_FAIL(hipMemcpyAsync(u, fields + N, sizeof(double) * N * c->lattice, kind, c->stream), "copy u");
+  if (T) HIP_OR_FAIL(hipMemcpyAsync(T, fields + 4 * N, sizeof(double) * N, kind, c->stream), "copy T");
   if (mem == LBM_HOST) HIP_OR_FAIL(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
   return LBM_OK;
 }

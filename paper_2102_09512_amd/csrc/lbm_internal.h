@@ -72,7 +72,7 @@ struct Ctx {
   Tile tile{};
   void* buf[2] = {nullptr, nullptr}; // population buffers (2Q x ps elements each)
   int cur = 0;                       // buffer holding the current state
-  double* fields = nullptr;          // 5 x N doubles, on first use: rho, ux, uy, uz, T
+  double* fields = nullptr;          // 5 x N doubles, staged initial fields: rho, ux, uy, uz, T
   double* work = nullptr;            // 10 x N doubles, on first use: new fields and staged host arrays
   double* partial = nullptr;         // per-block partial sums
   double* diag_dev = nullptr;        // final sums
