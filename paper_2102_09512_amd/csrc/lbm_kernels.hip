@@ -38,6 +38,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "lbm_internal.h"
 #include "lbm_node.h"
@@ -1167,91 +1168,112 @@ int default_chunk(int D, const int64_t n[3], int bx, int by) {
   return (int)(chunk < n[1] ? chunk : n[1]);
 }
 
-// A finer model of a launch, for the shapes whose results do not depend on the
+// Finer models of a launch, for the shapes whose results do not depend on the
 // march chunk (FP64, and 64 x 8 in FP32: one plane in flight, one copy of the
-// plane's arithmetic).  A work-group marches c planes of one tile column and
-// pays p1 planes for its start (launch, the planes next to the chunk, its first
-// loads); one that follows another on its compute unit pays less, p2.  The
-// device holds cap2 work-groups of the shape at a time; w2 is what a plane
-// takes them, and w1 what it takes up to cap1 of them, which share no SIMD.  A
-// round that leaves some compute units idle runs a little faster (`idle`;
-// D3Q27, where memory binds).  Fitted to sweeps of shape and chunk: the chosen
-// one is within 6% of the fastest of the sweep at 20x25x40, 64^3, 80^3, 96^3,
-// 100^3, 128^3, 160^3, 190x131x110, 192^3, 256^3, 256x256x32 and, in D2Q9, 800x4,
-// 300^2, 600x500, 1000x333, 200x1600, 1024^2, 2048^2.  Against the powers of two
-// of march_cost (us per step, same kernel): FP64 20x25x40 64x4/4 31.4, 32x8/1
-// 14.6; 100^3 64x4/32 285, 64x4/20 210; 190x131x110 64x4/16 600, 64x4/55 555;
-// 800x4 128x1/4 13.7, 128x1/1 7.3; 300^2 128x1/4 15.1, 128x1/1 10.7; FP32
-// 190x131x110 64x8/32 346, 64x8/22 296.
-struct ShapeModel {
-  int bx, by, cap1, cap2;
-  double w1, w2, p1, p2, idle;
+// plane's arithmetic).  Rounds are counted whole: work-groups of one launch take
+// equally long, so a few of them past a full round cost as much as a round
+// (priced as a fraction of one, FP64 224^3 took 2525 us a step in 784
+// work-groups of 32 x 8 and 56 planes, against 2120 in 224 of 64 x 4).
+
+// D3Q27: microseconds of a launch whose work-groups march c planes each, one
+// work-group per compute unit.  A round takes `plane` a plane, and `crowd` more
+// when all compute units march; a launch moves its planes, and `reread` planes
+// next to every chunk, at `cached` to `hbm` microseconds for one plane of all 256
+// tiles, in proportion to what of the two population buffers lies beyond
+// `cache` MB.  The two overlap in part (a sum of powers of 1.5).
+// Fitted to sweeps over 165 boxes in FP64 and 52 in FP32 from 10^4 to 1.7 10^7
+// nodes: 6-7% of a launch's time.
+struct MarchModel {
+  int bx, by, word;
+  double start, plane, crowd, cached, hbm, cache, reread, scale;
+
+  double time(const int64_t n[3], int64_t c) const {
+    const double tiles = (double)((n[0] + bx - 1) / bx) * (double)((n[1] + by - 1) / by);
+    const double blocks = tiles * (double)((n[2] + c - 1) / c), rounds = std::ceil(blocks / 256.0);
+    const double lanes = tiles * bx * by / ((double)n[0] * (double)n[1]);
+    const double megabytes = (double)n[0] * (double)n[1] * (double)n[2] * 2 * 54 * word * 1e-6;
+    const double move = cached + (hbm - cached) * std::max(0.0, 1.0 - cache / megabytes);
+    const double memory = blocks / 256.0 * ((double)c + reread) * move / std::sqrt(lanes);
+    const double march = rounds * (double)c * (plane + crowd * std::min(1.0, blocks / 256.0)) + (rounds - 1.0) * start;
+    return (4.0 + start + std::pow(std::pow(memory, 1.5) + std::pow(march, 1.5), 2.0 / 3.0)) * scale;
+  }
 };
+static const MarchModel kMarch3F64[] = {{64, 4, 8, 4.0, 5.5, 1.3, 2.7, 7.0, 120.0, 3.0, 1.0},
+                                        {32, 8, 8, 4.0, 5.5, 1.3, 2.7, 7.0, 120.0, 3.0, 1.05}};
+static const MarchModel kMarch64x8{64, 8, 4, 4.0, 7.0, 0.0, 4.5, 7.4, 160.0, 2.0, 1.0};
 
-static double launch_time(const ShapeModel& s, int64_t blocks, double c) {
-  auto filled = [&](int64_t b) { return 1.0 - s.idle * (1.0 - std::max(0.75, (double)b / s.cap2)); };
-  if (blocks <= s.cap2) return (blocks <= s.cap1 ? s.w1 : s.w2) * (c + s.p1) * filled(blocks);
-  const double rounds = (double)blocks / s.cap2;
-  // over many rounds a compute unit takes the next work-group as it gets free
-  if (rounds > 3.0) return s.w2 * ((c + s.p1) + (rounds - 1.0) * (c + s.p2));
-  const int64_t whole = blocks / s.cap2, rest = blocks % s.cap2;
-  double t = s.w2 * ((c + s.p1) + (double)(whole - 1) * (c + s.p2));
-  if (rest) t += (rest <= s.cap1 ? s.w1 : s.w2) * (c + s.p2) * filled(rest);
-  return t;
-}
+// D2Q9, in units of a row: a work-group marches c rows and pays p1 rows for its
+// start; one that follows another on its compute unit pays p2.  The device holds
+// cap2 work-groups of the shape at a time; w2 is what a row takes them, and w1
+// what it takes up to 256 of them, which share no SIMD.
+struct RowModel {
+  int bx, by, cap2;
+  double w1, w2, p1, p2;
 
-// One work-group per compute unit.
-static const ShapeModel kShape64x8{64, 8, 256, 256, 1.5, 1.5, 7.0, 6.0, 0.2};
-static const ShapeModel kShapes3F64[] = {{64, 4, 256, 256, 1.0, 1.0, 15.0, 13.0, 0.2},
-                                         {32, 8, 256, 256, 1.02, 1.02, 15.0, 13.0, 0.2}};
-// Two wavefronts per SIMD; two work-groups of a compute unit share SIMDs.
-static const ShapeModel kShape2F64[] = {{128, 1, 256, 1024, 1.03, 1.45, 3.0, 1.5, 0.0},
-                                        {256, 1, 256, 512, 1.06, 1.43, 3.0, 1.5, 0.0}};
+  double time(const int64_t n[3], int64_t c) const {
+    const int64_t blocks = ((n[0] + bx - 1) / bx) * ((n[1] + c - 1) / c), whole = blocks / cap2, rest = blocks % cap2;
+    const double last = rest ? (rest <= 256 ? w1 : w2) : 0.0;
+    if (!whole) return last * ((double)c + p1);
+    return w2 * ((double)c + p1) + (w2 * (double)(whole - 1) + last) * ((double)c + p2);
+  }
+};
+static const RowModel kRowsF64[] = {{128, 1, 1024, 1.03, 1.45, 3.0, 1.5}, {256, 1, 512, 1.06, 1.43, 3.0, 1.5}};
 
-// The model's best of the shapes and of the chunks of at most `longest` planes
-// that split the march axis evenly (longer ones gain nothing more).
-static Tile best_tile(const ShapeModel* shapes, int count, const int64_t n[3], int64_t nm, int64_t longest) {
-  Tile best{0, 0, 1};
-  double best_time = 0.0;
+// Of the shapes' chunks of at most `longest` planes that split the march axis
+// evenly (longer ones gain nothing more), the one that the model gives the
+// shortest time, if that is shorter than `base`'s by the factor `gain`; else base.
+// 1.07 up to 4 M nodes, where of 974 boxes with another choice than base one was
+// slower than base by more than 1.5% (2.0%), and the mean gain was 1.39 (D3Q27
+// FP64), 1.17 (64 x 8) and 1.31 (D2Q9).  Larger boxes are bound by memory more
+// than the models know: D3Q27 asks for 1.15 (with 1.07, 9 of 142 lost up to
+// 12%; with 1.15 none of 40), and D2Q9 keeps base (31 of 327 lost up to 12%).
+template <typename Model>
+static Tile refine(const Model* shapes, int count, const int64_t n[3], int64_t nm, int64_t longest, double gain,
+                   const Tile& base) {
+  Tile best = base;
+  double best_time = -1.0, base_time = -1.0;
   for (int k = 0; k < count; ++k) {
-    const ShapeModel& s = shapes[k];
-    const int64_t tiles = ((n[0] + s.bx - 1) / s.bx) * (s.by > 1 ? (n[1] + s.by - 1) / s.by : 1);
+    const Model& s = shapes[k];
+    if (s.bx == base.bx && s.by == base.by) base_time = s.time(n, base.chunk);
     for (int64_t c = 1; c <= longest && c <= nm; ++c) {
       const int64_t chunks = (nm + c - 1) / c;
       if ((nm + chunks - 1) / chunks != c) continue;
-      const double t = launch_time(s, tiles * chunks, (double)c);
-      if (!best.bx || t < best_time) {
+      const double t = s.time(n, c);
+      if (best_time < 0.0 || t < best_time) {
         best_time = t;
         best = Tile{s.bx, s.by, (int)c};
       }
     }
   }
-  return best;
+  return best_time * gain < base_time ? best : base;
 }
 
 // Default launch shape and march chunk (32 x 16 tiles, the 512-thread shape
 // with the smallest halo ring, measured 10% slower than 64 x 8 at 256^3 FP32
 // and are not compiled).  The caloric variant is compiled for one shape of each
 // lattice.
-// D3Q27 FP32: the shape with the lowest march_cost at its best chunk, and for
-// 64 x 8 (the only 512-thread shape that fits 256 registers without spilling)
-// the chunk of the finer model.  The 256-thread FP32 shapes keep two planes in
-// flight through a plane loop unrolled three times; the compiler fuses products
-// and sums a little differently in each copy, so there the rounding of a node
-// follows the chunk, and a different chunk moves the results of long runs, and
-// of runs with the bf16 corrector, by more than rounding (5e-5 of the deviations
-// after four corrections).  On one MI355X this picks 64 x 4 / 4 at 64^3, 64 x 8 /
-// 16 at 128^3 and for a 256 x 256 x 32 slab, 64 x 8 / 128 at 256^3 (9% faster
-// than 64 x 4 / 256 there).
+// D3Q27: the shape with the lowest march_cost at its best power-of-two chunk;
+// for FP64, and for 64 x 8 (the only 512-thread shape that fits 256 registers
+// without spilling), refined by the model.  The 256-thread FP32 shapes keep two
+// planes in flight through a plane loop unrolled three times; the compiler fuses
+// products and sums a little differently in each copy, so there the rounding of a
+// node follows the chunk, and a different chunk moves the results of long runs,
+// and of runs with the bf16 corrector, by more than rounding (5e-5 of the
+// deviations after four corrections).  On one MI355X this picks 64 x 4 / 4 at
+// FP32 64^3, 64 x 8 / 16 at 128^3 and for a 256 x 256 x 32 slab, 64 x 8 / 128 at
+// 256^3 (9% faster than 64 x 4 / 256 there).
 // D2Q9: rows of 128, or of 256 from 1024 nodes per row (FP32: 9% faster at
-// 4096^2, even at 1024^2 and 2048^2; FP64 at 1024^2: 4% faster).  FP32 keeps two
-// rows in flight, so its chunks stay as they are too.
+// 4096^2, even at 1024^2 and 2048^2; FP64 at 1024^2: 4% faster), FP64 refined by
+// the model.  FP32 keeps two rows in flight, so its chunks stay as they are too.
+// Microseconds a step, base and choice: FP64 20x25x40 64x4/4 31.4, 32x8/1 14.6;
+// 190x131x110 64x4/16 600, 64x4/55 555; 800x4 128x1/4 11.2, 128x1/1 6.2; 300^2
+// 128x1/4 15.1, 128x1/1 10.7; FP32 190x131x110 64x8/32 346, 64x8/22 296.
 Tile default_tile(int D, int precision, const int64_t n[3], bool caloric) {
+  const bool large = n[0] * n[1] * n[2] > 4000000;
   if (D == 3) {
-    if (precision == LBM_FP64) return best_tile(kShapes3F64, caloric ? 1 : 2, n, n[2], 256);
     struct Shape { int bx, by; double w; };
     const Shape shapes[3] = {{64, 4, 1.0}, {32, 8, 1.02}, {64, 8, 1.82}};
-    const int nshapes = caloric ? 1 : 3;
+    const int nshapes = caloric ? 1 : (precision == LBM_FP32_DEV ? 3 : 2);
     Tile best{64, 4, 1};
     double best_cost = -1.0;
     for (int s = 0; s < nshapes; ++s) {
@@ -1262,12 +1284,14 @@ Tile default_tile(int D, int precision, const int64_t n[3], bool caloric) {
         best = Tile{shapes[s].bx, shapes[s].by, (int)c};
       }
     }
-    return best.by == 8 && best.bx == 64 ? best_tile(&kShape64x8, 1, n, n[2], 256) : best;
+    const double gain = large ? 1.15 : 1.07;
+    if (precision == LBM_FP64) return refine(kMarch3F64, caloric ? 1 : 2, n, n[2], 256, gain, best);
+    return best.bx == 64 && best.by == 8 ? refine(&kMarch64x8, 1, n, n[2], 256, gain, best) : best;
   }
   const bool wide = !caloric && n[0] >= 1024;
-  if (precision == LBM_FP64) return best_tile(&kShape2F64[wide ? 1 : 0], 1, n, n[1], 32);
   const int bx = wide ? 256 : 128;
-  return Tile{bx, 1, default_chunk(D, n, bx, 1)};
+  const Tile base{bx, 1, default_chunk(D, n, bx, 1)};
+  return precision == LBM_FP64 && !large ? refine(&kRowsF64[wide ? 1 : 0], 1, n, n[1], 32, 1.07, base) : base;
 }
 
 // The 512-thread 64 x 8 shape exists for FP32 storage only: with FP64
