@@ -244,16 +244,17 @@ typedef struct lbm_batch_ctx* lbm_batch;
 
 /* Builds a batch over count >= 1 distinct handles (LBM_EINVAL if they differ
    in lattice, precision or device).  Allocates the device box table.  The
-   stream is the first handle's; the shared launch tile is the lattice's
-   default with per-box march chunks. */
+   stream is the first handle's; the shared launch tile is a default of the
+   first box, with march chunks chosen for the boxes together. */
 int lbm_batch_create(lbm_batch* out, const lbm_handle* boxes, int count);
 /* Frees the batch (not the handles).  NULL is accepted. */
 int lbm_batch_destroy(lbm_batch b);
 /* Stream on which lbm_batch_step orders its work (after earlier work on it). */
 int lbm_batch_set_stream(lbm_batch b, void* hip_stream);
 /* Shared launch tile {bx, by, chunk}: bx, by one of the compiled shapes of the
-   lattice (as in lbm_options.tile); chunk > 0 for every box, 0 for each box's
-   default chunk with that shape.  LBM_EINVAL if not available.  Drops a
+   lattice (as in lbm_options.tile); chunk > 0 for every box, 0 for chunks
+   chosen for the boxes together: what a box takes alone on the device is too
+   short for many boxes that share it.  LBM_EINVAL if not available.  Drops a
    captured graph. */
 int lbm_batch_set_tile(lbm_batch b, const int tile[3]);
 int lbm_batch_get_tile(lbm_batch b, int tile[3]);

@@ -685,16 +685,16 @@ using Batch = lbm_batch_ctx;
 // the table (synchronous on the caller's stream); drops a captured graph.
 int batch_layout(Batch* b) {
   int64_t total = 0;
+  if (b->tile.chunk <= 0 && (b->chunk_shape.bx != b->tile.bx || b->chunk_shape.by != b->tile.by)) {
+    lbm::batch_chunks(b->lattice, b->precision, b->extents.data(), (int)b->boxes.size(), b->tile.bx, b->tile.by,
+                      b->chunk.data());
+    b->chunk_shape = b->tile;
+  }
   for (size_t i = 0; i < b->boxes.size(); ++i) {
     const lbm::Ctx* c = b->boxes[i];
     lbm::Tile t = b->tile;
+    if (t.chunk <= 0) t.chunk = b->chunk[i];
     const int64_t nm = c->lattice == 3 ? c->n[2] : c->n[1];
-    if (t.chunk <= 0 && b->auto_tile && c->lattice == 3) {
-      // the chunk that the box has on its own, where it has this shape there
-      const lbm::Tile own = lbm::default_tile(c->lattice, c->precision, c->n);
-      if (own.bx == t.bx && own.by == t.by) t.chunk = own.chunk;
-    }
-    if (t.chunk <= 0) t.chunk = lbm::default_chunk(c->lattice, c->n, t.bx, t.by);
     if (t.chunk > nm) t.chunk = (int)nm;
     lbm::BoxEntry& e = b->host[i];
     fill_step_params(c, t, e.p);
@@ -796,8 +796,9 @@ int lbm_batch_create(lbm_batch* out, const lbm_handle* boxes, int count) {
   b->host.resize(count);
   b->cur_dev.assign(count, 0);
   b->user_stream = boxes[0]->stream;
-  const lbm::Tile t0 = lbm::default_tile(b->lattice, b->precision, boxes[0]->n);
-  b->tile = {t0.bx, t0.by, 0};
+  b->chunk.assign(count, 0);
+  for (const lbm::Ctx* c : b->boxes) b->extents.push_back({{c->n[0], c->n[1], c->n[2]}});
+  b->tile = lbm::batch_shape(b->lattice, b->precision, b->extents.data(), count);
   int rc = batch_select_device(b);
   hipError_t e = hipSuccess;
   if (rc == LBM_OK) e = hipMalloc(&b->table, sizeof(lbm::BoxEntry) * (size_t)count);
@@ -843,7 +844,6 @@ int lbm_batch_set_tile(lbm_batch b, const int tile[3]) {
   int rc = batch_select_device(b);
   if (rc != LBM_OK) return rc;
   b->tile = t;
-  b->auto_tile = false;
   return batch_layout(b);
 }
 
@@ -884,7 +884,6 @@ int lbm_batch_tune(lbm_batch b, int reps, double* best_ms) {
   }
   // Every timed launch reads each box's current buffer and writes the other
   // one (flip 0, no toggle), so the states are left as they were.
-  const bool auto_tile = b->auto_tile;
   lbm::Tile best = b->tile;
   bool best_persistent = b->persistent;
   float best_t = -1.0f;
@@ -915,7 +914,6 @@ int lbm_batch_tune(lbm_batch b, int reps, double* best_ms) {
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
   b->tile = best;
-  b->auto_tile = auto_tile && best.chunk == 0;
   b->persistent = best_persistent;
   const int rc2 = batch_layout(b);
   if (rc != LBM_OK) return rc;

@@ -96,6 +96,10 @@ struct DiagGrid {
   bool flat;  // 256 nodes in memory order instead of tiles
 };
 
+struct Extent {
+  int64_t n[3];
+};
+
 // One box of a batched launch (an entry of the device box table).
 struct BoxEntry {
   StepParams p;       // the box's step parameters for the batch tile
@@ -111,9 +115,11 @@ struct Batch {
   std::vector<BoxEntry> host;      // host image of the table
   BoxEntry* table = nullptr;       // device table
   std::vector<int> cur_dev;        // cur of each box as the device table holds it
+  std::vector<Extent> extents;     // of every box
+  std::vector<int> chunk;          // batch_chunks of the shape chunk_shape
+  Tile chunk_shape{};
   int total_blocks = 0;
-  Tile tile{};                     // bx, by shared by all boxes; chunk 0 = per-box default
-  bool auto_tile = true;           // the default tile (none set or tuned)
+  Tile tile{};                     // bx, by shared by all boxes; chunk 0 = chosen for them (batch_chunks)
   bool persistent = false;         // fixed grid looping over the tiles instead of one work-group per tile
   hipStream_t user_stream = nullptr;
   hipStream_t own_stream = nullptr;  // graph replays run here
@@ -168,6 +174,10 @@ hipError_t launch_toggle(const Batch& b, hipStream_t s);
 // given shape, and whether a tile is available.
 Tile default_tile(int D, int precision, const int64_t n[3], bool caloric = false);
 int default_chunk(int D, const int64_t n[3], int bx, int by);
+// The launch shape (chunk 0) of a batch, and its boxes' chunks in a shape
+// (returns the modelled time, 0 without a model).
+Tile batch_shape(int D, int precision, const Extent* box, int count);
+double batch_chunks(int D, int precision, const Extent* box, int count, int bx, int by, int* chunk);
 bool tile_supported(int D, int precision, const Tile& t, bool caloric = false);
 // Whether the persistent form of the batched launch exists for a tile.
 bool persistent_supported(const Tile& t);
