@@ -319,7 +319,7 @@ int lbm_create(lbm_handle* out, int lattice, const int64_t dims[3], double gamma
   if (opt.tile[0] || opt.tile[1] || opt.tile[2]) {
     lbm::Tile t{opt.tile[0] ? opt.tile[0] : tile.bx, opt.tile[1] ? opt.tile[1] : tile.by, opt.tile[2]};
     if (lattice == LBM_D2Q9 && !opt.tile[1]) t.by = 1;
-    if (!t.chunk && t.bx > 0 && t.by > 0) t.chunk = lbm::default_chunk(lattice, dims, t.bx, t.by);
+    if (!t.chunk && t.bx > 0 && t.by > 0) t.chunk = lbm::shape_chunk(lattice, opt.precision, dims, t.bx, t.by, caloric);
     if (!lbm::tile_supported(lattice, opt.precision, t, caloric) || t.chunk < 1)
       return fail(LBM_EINVAL, caloric ? "lbm_create: with cv_poly only the default launch shape is compiled"
                                       : "lbm_create: launch tile not available");

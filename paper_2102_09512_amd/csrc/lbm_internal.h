@@ -170,9 +170,11 @@ int corrector_planes(Ctx* c, float* x);
 int corrector_apply(Ctx* c, const float* y, const float* sd, int channels, int offset, float limit);
 hipError_t launch_batch_step(const Batch& b, hipStream_t s, int flip);
 hipError_t launch_toggle(const Batch& b, hipStream_t s);
-// Default launch tile for a lattice/precision, the default march chunk for a
-// given shape, and whether a tile is available.
+// Default launch tile for a lattice/precision, the chunk that goes with a given
+// shape (the default's own where that is its shape), the power-of-two rule that both start
+// from, and whether a tile is available.
 Tile default_tile(int D, int precision, const int64_t n[3], bool caloric = false);
+int shape_chunk(int D, int precision, const int64_t n[3], int bx, int by, bool caloric = false);
 int default_chunk(int D, const int64_t n[3], int bx, int by);
 // The launch shape (chunk 0) of a batch, and its boxes' chunks in a shape
 // (returns the modelled time, 0 without a model).

@@ -1330,6 +1330,12 @@ Tile default_tile(int D, int precision, const int64_t n[3], bool caloric) {
   return refined(D, precision, n, base_tile(D, precision, n, caloric), !caloric);
 }
 
+int shape_chunk(int D, int precision, const int64_t n[3], int bx, int by, bool caloric) {
+  const Tile own = default_tile(D, precision, n, caloric);
+  if (own.bx == bx && own.by == by) return own.chunk;
+  return refined(D, precision, n, Tile{bx, by, default_chunk(D, n, bx, by)}, false).chunk;
+}
+
 // The modelled time of a batch's launch in a shape, 0 where the shape has no model.
 static double modelled(int D, int precision, int bx, const Load& l) {
   if (precision == LBM_FP32_DEV) return D == 3 ? kMarch64x8.time(l) : 0.0;
