@@ -78,7 +78,8 @@ typedef struct {
   double rho_ref;       /* reference density of FP32 deviations; default 1 */
   int deriv_scheme;     /* LBM_DERIV_UPWIND (default) or LBM_DERIV_CENTRAL */
   int tile[3];          /* launch shape of the step kernel: x width, y width (D3Q27), march chunk; 0 = default
-                           (a zero chunk with a given shape: the default chunk for that shape).  Shapes:
+                           (a zero chunk with a given shape: the default's where that is its shape, else
+                           a power of two or the whole axis, chosen for the shape).  Shapes:
                            D3Q27 64x4, 32x8 and, for LBM_FP32_DEV only, 64x8; D2Q9 64, 128, 256 wide */
   double u_ref[3];      /* reference velocity of FP32 deviations (|u_ref_a| < 1); default 0 */
   double cv_poly[3];    /* caloric law (Sec. II.A, Eq. (6)): C_v(T) = cv_poly[0] + cv_poly[1] T + cv_poly[2] T^2,

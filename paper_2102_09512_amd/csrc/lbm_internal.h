@@ -171,8 +171,8 @@ int corrector_apply(Ctx* c, const float* y, const float* sd, int channels, int o
 hipError_t launch_batch_step(const Batch& b, hipStream_t s, int flip);
 hipError_t launch_toggle(const Batch& b, hipStream_t s);
 // Default launch tile for a lattice/precision, the chunk that goes with a given
-// shape (the default's own where that is its shape), the power-of-two rule that both start
-// from, and whether a tile is available.
+// shape (the default's own where that is its shape, else default_chunk's power of two),
+// and whether a tile is available.
 Tile default_tile(int D, int precision, const int64_t n[3], bool caloric = false);
 int shape_chunk(int D, int precision, const int64_t n[3], int bx, int by, bool caloric = false);
 int default_chunk(int D, const int64_t n[3], int bx, int by);

@@ -1332,8 +1332,7 @@ Tile default_tile(int D, int precision, const int64_t n[3], bool caloric) {
 
 int shape_chunk(int D, int precision, const int64_t n[3], int bx, int by, bool caloric) {
   const Tile own = default_tile(D, precision, n, caloric);
-  if (own.bx == bx && own.by == by) return own.chunk;
-  return refined(D, precision, n, Tile{bx, by, default_chunk(D, n, bx, by)}, false).chunk;
+  return own.bx == bx && own.by == by ? own.chunk : default_chunk(D, n, bx, by);
 }
 
 // The modelled time of a batch's launch in a shape, 0 where the shape has no model.
