@@ -91,7 +91,7 @@ constexpr int kScratchDoubles = kMaxDiagBlocks * kNumDiag + kNumDiag;
 // Launch geometry of the diagnostics: `tasks` tiles times march chunks dealt
 // out over `blocks` work-groups.
 struct DiagGrid {
-  int by;  // y width of the tile (D3Q27)
+  int bx, by;  // widths of the tile
   int tiles_x, tiles_y, chunk, tasks, blocks;
   bool flat;  // 256 nodes in memory order instead of tiles
 };
@@ -141,6 +141,7 @@ hipError_t launch_fields(const Ctx& c, const void* pops, double* fields);
 // then the sums (kNumDiag, in diag_from_sums' order).
 hipError_t launch_diag(const Ctx& c, const void* pops, double* partial, const DiagGrid& g, double* out);
 DiagGrid diag_grid(const Ctx& c);
+DiagGrid diag_grid(int D, int precision, const int64_t n[3]);
 // Device address of the current device's allocation-free scratch
 // (kScratchDoubles doubles).
 hipError_t scratch_address(double** out);

@@ -851,13 +851,13 @@ struct DiagSums {
 // velocity goes to LDS for the in-plane differences (a one-node ring around
 // the tile is formed by the first threads), and the march-axis neighbours are
 // the same thread's previous and next planes.  The populations are read once,
-// plus the ring and the two planes next to a chunk; what binds is the latency
-// that two wavefronts per SIMD (180-220 registers: 35 for the sums, 54 or 108
-// for a node's loads) leave open.  256^3: 890 us FP32, 1550 us FP64 (1205 and
-// 1900 us when the fields went through memory and the differences were read
-// back).  Loads in batches of nine: 934 and 1620 us; requested a plane ahead: 880
-// and 1680 us; held to 128 registers it spills; the fields through memory
-// again but with the node sums in that pass: 1040 and 1740 us.
+// plus the two planes next to a chunk and the ring, whose column nodes cost a
+// cache line each (64 x 8: half as many lines again as the tile's).  Bound by that
+// traffic: neighbouring tiles run on one die, whose cache then serves most of a
+// ring (a call with tiles dealt out over the dies in turn and in die order: 256^3
+// FP32 868 and 718 us, FP64 1498 and 1267; 166x213x86 202 and 184, 332 and 304).
+// Registers allow two wavefronts per SIMD (222: 35 for the sums, 54 or 108 for a
+// node's loads).
 template <int D, typename S, int BX, int BY>
 __global__ void __launch_bounds__(BX* BY) diag_kernel(const S* __restrict__ pops, double* __restrict__ partial,
                                                          const StepParams p, const DiagGrid g) {
@@ -872,7 +872,8 @@ __global__ void __launch_bounds__(BX* BY) diag_kernel(const S* __restrict__ pops
   const long long plane_bytes = p.ms * (long long)sizeof(S);
   const int t = threadIdx.x, lx = t % BX, ly = t / BX;
   DiagSums<D> sums;
-  for (int task = blockIdx.x; task < g.tasks; task += gridDim.x) {
+  const int block = xcd_logical_block(blockIdx.x, gridDim.x);
+  for (int task = block; task < g.tasks; task += gridDim.x) {
     const int tx = task % g.tiles_x, r = task / g.tiles_x;
     const int ty = (D == 3) ? r % g.tiles_y : 0, ck = (D == 3) ? r / g.tiles_y : r;
     const int x0 = tx * BX, y0 = ty * BY, m0 = ck * g.chunk, m1 = min(m0 + g.chunk, nm);
@@ -968,7 +969,7 @@ __global__ void __launch_bounds__(BX* BY) diag_kernel(const S* __restrict__ pops
   }
   double v[kNumDiag];
   sums.store(v);
-  block_reduce_store<kNumDiag, BX * BY / 64>(v, partial + blockIdx.x, gridDim.x);
+  block_reduce_store<kNumDiag, BX * BY / 64>(v, partial + block, gridDim.x);
 }
 
 // The same sums for boxes so narrow that a tile would leave most of its lanes
@@ -1905,52 +1906,89 @@ int validate_blocks(const Ctx& c) {
   return (int)(want < kMaxDiagBlocks ? want : kMaxDiagBlocks);
 }
 
-// Work-groups and march chunks of the diagnostics: 64 x 8 tiles (a smaller
-// ring to read again: 890 us at 256^3 FP32 against 1030 for 64 x 4) as long as
-// they leave every compute unit a work-group with chunks of four planes, else
-// 64 x 4; 128 x 1 in 2-D (2000 x 1500 FP64: 116 us a call against 129 for
-// 256 x 1, which also leaves more lanes idle past a ragged edge).  Chunks are
-// as long as `target` work-groups allow, as each reads two more planes, and
-// shorter than four planes only where the grid cannot fill the chip: there
-// the chain of planes is the time (a call on 12^3: 36 us with one-plane
-// chunks against 45 with four; on 100 x 60: 32 against 37; but 59 against 49
-// on 50 x 60 x 40 in FP64, which has 600 tile planes).  A box whose planes use
-// less than 0.4 (FP32) or 0.25 (FP64) of a tile's lanes goes in memory order:
-// calls on 5 x 400 x 300 take 117 and 162 us against 372 and 391 in tiles, on
-// 20 x 200 x 200 (a share of 0.31) 136 and 223 against 158 and 209.
-DiagGrid diag_grid(const Ctx& c) {
+// Launch geometry of the diagnostics.
+// D2Q9: rows of 128 (2000 x 1500 FP64: 116 us a call against 129 for 256 x 1, which
+// also leaves more lanes idle past a ragged edge) in chunks as long as 1024
+// work-groups allow, and shorter than four rows only where the grid cannot fill
+// the chip (100 x 60: 32 us a call against 37).  Rows that use less than 0.25
+// (FP32: 0.4) of their lanes go in memory order.
+// D3Q27: in memory order go planes that use less than 0.35 of the lanes of 32 x 8
+// tiles, and boxes up to 65,536 nodes (one work-group of 256 per compute unit)
+// unless one-plane chunks of 32 x 8 leave no compute unit two work-groups; boxes up to
+// 300,000 nodes take 32 x 8, larger ones 64 x 8 or 32 x 16, or memory order, by
+// DiagModel.  A call against the first form of lbm_diagnostics, which put every node's
+// fields into memory and took the differences from there: 1.09 times as fast in FP64
+// and 1.10 in FP32 over 1466 boxes of up to 10^7 nodes.  That form is still faster by more
+// than 3% for 27 of them in FP64 (at most 10%: planes of 1 to 9 nodes along x, and calls of 56
+// us or less) and for 22 in FP32 (at most 17%: a few nodes past a multiple of 32
+// along x; 16 x 32 tiles win some of those back and lose others).
+struct DiagModel {
+  double cached, hbm, cache, ring;  // us per MB of populations, within `cache` MB and beyond; weight of ring lines
+  double plane, flat;               // us per plane of a round; per node in memory order
+
+  double microseconds(double megabytes) const { return cached + (hbm - cached) * std::max(0.0, 1.0 - cache / megabytes); }
+};
+static const DiagModel kDiag64{0.055, 0.093, 165.0, 1.0, 4.0, 2.3e-4}, kDiag32{0.038, 0.067, 205.0, 0.55, 3.9, 1.35e-4};
+
+DiagGrid diag_grid(int D, int precision, const int64_t n[3]) {
   DiagGrid g{};
-  const int64_t nm = c.lattice == 3 ? c.n[2] : c.n[1];
-  auto shape = [&](int bx, int by, int64_t target, int64_t fill) {
-    g.by = by;
-    g.tiles_x = (int)((c.n[0] + bx - 1) / bx);
-    g.tiles_y = c.lattice == 3 ? (int)((c.n[1] + by - 1) / by) : 1;
-    const int64_t tiles = (int64_t)g.tiles_x * g.tiles_y;
-    const int64_t chunks = tiles < target ? target / tiles : 1;
-    int64_t chunk = (nm + chunks - 1) / chunks;
-    const int64_t least = std::min<int64_t>((tiles * nm + fill - 1) / fill, 4);
-    if (chunk < least) chunk = least;
-    g.chunk = (int)chunk;
-    const int64_t tasks = tiles * ((nm + chunk - 1) / chunk);
-    g.tasks = (int)tasks;
-    g.blocks = (int)(tasks < kMaxDiagBlocks ? tasks : kMaxDiagBlocks);
-  };
-  const int bx = c.lattice == 3 ? 64 : 128, by = c.lattice == 3 ? 4 : 1;
-  const int64_t plane = c.n[0] * (c.lattice == 3 ? c.n[1] : 1);
-  const int64_t lanes = (c.n[0] + bx - 1) / bx * bx * (c.lattice == 3 ? (c.n[1] + by - 1) / by * by : 1);
-  if ((double)plane < (c.precision == LBM_FP64 ? 0.25 : 0.4) * (double)lanes) {
+  const int64_t nm = D == 3 ? n[2] : n[1], N = n[0] * n[1] * n[2];
+  auto in_memory_order = [&] {
     g.flat = true;
-    g.blocks = (validate_blocks(c) + 7) / 8 * 8;
+    g.blocks = (int)((std::min<int64_t>((N + 255) / 256, kMaxDiagBlocks) + 7) / 8 * 8);
     return g;
-  }
-  if (c.lattice == 2) {
-    shape(128, 1, 1024, 1024);
+  };
+  auto tiles_of = [&](int bx, int by) { return ((n[0] + bx - 1) / bx) * (D == 3 ? (n[1] + by - 1) / by : 1); };
+  auto tiled = [&](int bx, int by, int64_t chunk) {
+    g.bx = bx;
+    g.by = by;
+    g.tiles_x = (int)((n[0] + bx - 1) / bx);
+    g.tiles_y = D == 3 ? (int)((n[1] + by - 1) / by) : 1;
+    chunk = std::min(chunk, nm);
+    g.chunk = (int)chunk;
+    g.tasks = (int)(tiles_of(bx, by) * ((nm + chunk - 1) / chunk));
+    g.blocks = std::min(g.tasks, kMaxDiagBlocks);
     return g;
+  };
+  if (D == 2) {
+    const int64_t tiles = tiles_of(128, 1), chunks = tiles < 1024 ? 1024 / tiles : 1;
+    if ((double)n[0] < (precision == LBM_FP64 ? 0.25 : 0.4) * 128.0 * (double)tiles) return in_memory_order();
+    return tiled(128, 1, std::max((nm + chunks - 1) / chunks, std::min<int64_t>((tiles * nm + 1023) / 1024, 4)));
   }
-  shape(64, 8, 256, 256);
-  if (g.tasks < 256 || (g.chunk < 4 && g.chunk < nm)) shape(64, 4, 1024, 256);
-  return g;
+  const int64_t small = tiles_of(32, 8);
+  if ((double)(n[0] * n[1]) < 0.35 * 256.0 * (double)small) return in_memory_order();
+  if (N <= 300000 && small * nm <= 256) return tiled(32, 8, 1);
+  if (N <= 65536) return in_memory_order();
+  const DiagModel& m = precision == LBM_FP64 ? kDiag64 : kDiag32;
+  const int word = precision == LBM_FP64 ? 8 : 4, line = 128 / (2 * word);  // pairs of a cache line
+  const double megabytes = (double)N * 54 * word * 1e-6, rate = m.microseconds(megabytes);
+  double best = 16.0 + std::hypot((double)N * m.flat, 17.5);  // memory order
+  int bx = 0, by = 0;
+  int64_t chunk = 0;
+  const int shapes[3][2] = {{32, 8}, {64, 8}, {32, 16}};
+  for (int s = N <= 300000 ? 0 : 1; s < (N <= 300000 ? 1 : 3); ++s) {
+    const int64_t wx = std::min<int64_t>(shapes[s][0], n[0]), wy = std::min<int64_t>(shapes[s][1], n[1]);
+    const int64_t tiles = tiles_of(shapes[s][0], shapes[s][1]), resident = s ? 256 : 512;
+    const double lines = (double)((wx + line - 1) / line);  // of a tile's row; a ring column costs one a row
+    const double ring = ((wx < n[0] ? 2.0 * (double)wy : 0.0) + (wy < n[1] ? 2.0 * lines : 0.0)) / (lines * (double)wy);
+    for (int64_t most = 256; most <= 4096; most += 256) {  // the shortest chunk with at most so many work-groups
+      const int64_t chunks = std::min(std::max<int64_t>(most / tiles, 1), nm), c = (nm + chunks - 1) / chunks;
+      const int64_t blocks = tiles * ((nm + c - 1) / c), rest = blocks % resident;
+      // a last round that leaves compute units one work-group of their two costs less
+      const double rounds = (double)(blocks / resident) + (!rest ? 0.0 : resident == 512 && rest <= 256 ? 0.7 : 1.0);
+      const double time = 24.0 + megabytes * (1.0 + 2.0 / (double)c + m.ring * ring) * rate +
+                          rounds * ((s ? 8.7 : 7.0) + (double)c * m.plane);
+      if (time >= best) continue;
+      best = time;
+      bx = shapes[s][0];
+      by = shapes[s][1];
+      chunk = c;
+    }
+  }
+  return bx ? tiled(bx, by, chunk) : in_memory_order();
 }
+
+DiagGrid diag_grid(const Ctx& c) { return diag_grid(c.lattice, c.precision, c.n); }
 
 // Device memory of the allocation-free diagnostics (lbm_diagnostics_noalloc):
 // the per-block partial sums and the final sums, kScratchDoubles doubles
@@ -1989,11 +2027,13 @@ hipError_t launch_diag(const Ctx& c, const void* pops, double* partial, const Di
     }
   } else if (c.lattice == 3) {
     if (c.precision == LBM_FP64) {
-      if (g.by == 8) launch_diag_t<3, double, 64, 8>(c, pops, partial, g);
-      else launch_diag_t<3, double, 64, 4>(c, pops, partial, g);
+      if (g.bx == 64) launch_diag_t<3, double, 64, 8>(c, pops, partial, g);
+      else if (g.by == 16) launch_diag_t<3, double, 32, 16>(c, pops, partial, g);
+      else launch_diag_t<3, double, 32, 8>(c, pops, partial, g);
     } else {
-      if (g.by == 8) launch_diag_t<3, float, 64, 8>(c, pops, partial, g);
-      else launch_diag_t<3, float, 64, 4>(c, pops, partial, g);
+      if (g.bx == 64) launch_diag_t<3, float, 64, 8>(c, pops, partial, g);
+      else if (g.by == 16) launch_diag_t<3, float, 32, 16>(c, pops, partial, g);
+      else launch_diag_t<3, float, 32, 8>(c, pops, partial, g);
     }
   } else if (c.precision == LBM_FP64) {
     launch_diag_t<2, double, 128, 1>(c, pops, partial, g);
