@@ -238,7 +238,11 @@ int lbm_device_copy(void* dst, const void* src, size_t bytes, void* hip_stream);
    precision, one device) by one kernel launch per time step: the launch's
    work-groups are dealt out over all boxes' tiles through a device table, and
    every box computes exactly what lbm_step would (same kernel body, same
-   per-box parameters, so the same result to the last bit for FP32 storage).
+   per-box parameters).  With FP32 storage that is the same result to the last
+   bit for a handle stepped alone in the batch's shape and chunk: all boxes share
+   the first one's shape, and the rounding of the FP32 shapes of 256 work-items
+   follows shape and chunk, so a box whose own default is another shape
+   (lbm_get_tile) differs from its lbm_step in the last bits.
    The batch does not own the handles: they stay usable on their own (init,
    moments, diagnostics, checkpoints, lbm_step) and must outlive the batch. */
 typedef struct lbm_batch_ctx* lbm_batch;
@@ -253,7 +257,7 @@ int lbm_batch_destroy(lbm_batch b);
 /* Stream on which lbm_batch_step orders its work (after earlier work on it). */
 int lbm_batch_set_stream(lbm_batch b, void* hip_stream);
 /* Shared launch tile {bx, by, chunk}: bx, by one of the compiled shapes of the
-   lattice (as in lbm_options.tile); chunk > 0 for every box, 0 for chunks
+   lattice (as in lbm_options.tile), which FP32 rounding follows (see above); chunk > 0 for every box, 0 for chunks
    chosen for the boxes together: what a box takes alone on the device is too
    short for many boxes that share it.  LBM_EINVAL if not available.  Drops a
    captured graph. */
