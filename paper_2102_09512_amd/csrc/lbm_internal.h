@@ -162,7 +162,7 @@ hipError_t launch_correct(const Ctx& c, void* pops, const float* y, const float*
 // The new fields keep * old + d into newf, and the number of bad nodes into out.
 hipError_t launch_fields_new(const Ctx& c, const void* pops, const double* drho, const double* du, const double* dT,
                              bool keep, double* newf, double* partial, int nblocks, double* out);
-// rho, u, T as FP32 planes x[D + 2][N].
+// rho, u, T as FP32 planes x[5][N] (D3Q27, as launch_correct).
 hipError_t launch_planes(const Ctx& c, const void* pops, float* x);
 hipError_t launch_filter(const Ctx& c, const void* pops, int factor, double* rho, double* u, double* T);
 // Corrector support (host, lbm_api.hip): the state's input planes, and a

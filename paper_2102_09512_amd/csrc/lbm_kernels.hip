@@ -1627,9 +1627,8 @@ struct NewFields {
 };
 
 // ... or the old ones and the normalised corrections y[c][n], output c for
-// field off + c (0 rho, 1..D u, D + 1 T); with limit > 0 a correction is
-// clipped to [-limit, limit] first.
-template <int D>
+// field off + c (0 rho, 1..3 u, 4 T); with limit > 0 a correction is clipped to
+// [-limit, limit] first.  Networks have D3Q27's three axes.
 struct Corrected {
   const float *y, *sd;
   int C, off;
@@ -1637,7 +1636,7 @@ struct Corrected {
   long long N;
   __device__ inline void operator()(long long n, double& rho, double* u, double& T) const {
 #pragma unroll
-    for (int f = 0; f < D + 2; ++f) {
+    for (int f = 0; f < 5; ++f) {
       const int c = f - off;
       double inc = 0.0;
       if (c >= 0 && c < C) {
@@ -1646,7 +1645,7 @@ struct Corrected {
         inc = (double)v * sd[c];
       }
       if (f == 0) rho += inc;
-      else if (f <= D) u[f - 1] += inc;
+      else if (f <= 3) u[f - 1] += inc;
       else T += inc;
     }
   }
@@ -1730,21 +1729,21 @@ __global__ void __launch_bounds__(256) fields_new_kernel(const S* __restrict__ p
   block_reduce_store<1, 4>(bad, partial + blockIdx.x, 1);
 }
 
-// rho, u, T as the FP32 input planes x[D + 2][N] of the corrector.
-template <int D, typename S>
+// rho, u, T as the FP32 input planes x[5][N] of the corrector (D3Q27).
+template <typename S>
 __global__ void __launch_bounds__(256) planes_kernel(const S* __restrict__ pops, float* __restrict__ x, int N,
                                                      const StepParams p) {
   const int n = blockIdx.x * blockDim.x + threadIdx.x;
   if (n >= N) return;
-  typename Buf<S>::pair_t v[lat_q(D)];
-  load_pairs<D>(pops + pair_offset(p, n), p, v);
+  typename Buf<S>::pair_t v[lat_q(3)];
+  load_pairs<3>(pops + pair_offset(p, n), p, v);
   double s0, j[3], se, rho, u[3], T, rhoE;
-  pair_sums<D>(v, s0, j, &se);
-  fields_of<D>(p, s0, j, se, rho, u, T, rhoE);
+  pair_sums<3>(v, s0, j, &se);
+  fields_of<3>(p, s0, j, se, rho, u, T, rhoE);
   x[n] = (float)rho;
 #pragma unroll
-  for (int a = 0; a < D; ++a) x[(long long)(1 + a) * N + n] = (float)u[a];
-  x[(long long)(1 + D) * N + n] = (float)T;
+  for (int a = 0; a < 3; ++a) x[(long long)(1 + a) * N + n] = (float)u[a];
+  x[4LL * N + n] = (float)T;
 }
 
 // Coarse nodes: means of rho, rho u and rho E over factor^D fine nodes,
@@ -1826,8 +1825,7 @@ hipError_t launch_fields_add(const Ctx& c, void* pops, const double* newf) {
 
 hipError_t launch_correct(const Ctx& c, void* pops, const float* y, const float* sd, int channels, int offset,
                           float limit) {
-  if (c.lattice == 3) return launch_add_t<3>(c, pops, Corrected<3>{y, sd, channels, offset, limit, c.N});
-  return launch_add_t<2>(c, pops, Corrected<2>{y, sd, channels, offset, limit, c.N});
+  return launch_add_t<3>(c, pops, Corrected{y, sd, channels, offset, limit, c.N});
 }
 
 template <int D, typename S>
@@ -1852,17 +1850,15 @@ hipError_t launch_fields_new(const Ctx& c, const void* pops, const double* drho,
   return hipGetLastError();
 }
 
-template <int D, typename S>
+template <typename S>
 static hipError_t launch_planes_t(const Ctx& c, const void* pops, float* x) {
-  hipLaunchKernelGGL((planes_kernel<D, S>), dim3((unsigned)((c.N + 255) / 256)), dim3(256), 0, c.stream,
+  hipLaunchKernelGGL(planes_kernel<S>, dim3((unsigned)((c.N + 255) / 256)), dim3(256), 0, c.stream,
                      static_cast<const S*>(pops), x, (int)c.N, c.sp);
   return hipGetLastError();
 }
 
 hipError_t launch_planes(const Ctx& c, const void* pops, float* x) {
-  if (c.lattice == 3)
-    return c.precision == LBM_FP64 ? launch_planes_t<3, double>(c, pops, x) : launch_planes_t<3, float>(c, pops, x);
-  return c.precision == LBM_FP64 ? launch_planes_t<2, double>(c, pops, x) : launch_planes_t<2, float>(c, pops, x);
+  return c.precision == LBM_FP64 ? launch_planes_t<double>(c, pops, x) : launch_planes_t<float>(c, pops, x);
 }
 
 template <int D, typename S>

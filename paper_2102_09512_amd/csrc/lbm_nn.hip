@@ -1477,6 +1477,7 @@ int lbm_nn_correct(lbm_nn n, lbm_handle h) {
   const int D = h->lattice;
   if (n->ch[0] != D + 2 || n->out_off + n->ch[n->L] > D + 2)
     return nn_fail(LBM_EINVAL, "lbm_nn_correct: the network must read the D + 2 fields and correct fields among them");
+  if (D != 3) return nn_fail(LBM_EINVAL, "lbm_nn_correct: networks are three-dimensional, the handle is not");
   if (h->n[0] != n->g.nx || h->n[1] != n->g.ny || h->n[2] != n->g.nz)
     return nn_fail(LBM_EINVAL, "lbm_nn_correct: grid of the handle differs from the network's");
   int rc = nn_select(n);
