@@ -1654,10 +1654,14 @@ struct Corrected {
 // f_i += f^eq_i(new) - f^eq_i(old), g likewise (equilibria evaluated in FP64
 // for either storage), the old fields those of the populations themselves.
 // Where the new fields are the old ones, the populations keep every bit.
-// The populations are read and written once; with two equilibria a node in
-// 2 x 60 registers, FP64 arithmetic and the latency of a few wavefronts bind
-// at the corrector's 64^3: 29.6 us (45.2 us with the old fields from memory and
-// both equilibria whole in registers, and 28 us for the kernels around it).
+// Two equilibria a node take 2 x 64 registers beside the pairs' 54 (FP32) or 108,
+// so FP64 arithmetic and the latency of two wavefronts per SIMD bind.  The
+// populations are written once and read once, but for the last two rows of D3Q27
+// in FP32, which are read again: held, they would put 52 bytes a lane into scratch
+// memory.  lbm_nn_correct with a one-layer network at 64^3: 51.2 us (53.7 with all rows
+// held, 58.8 with none; FP64 69.6, 72.7, 83.6), of which this kernel takes about half
+// (45.2 us with the old fields from memory and both equilibria whole in registers,
+// and 28 us for the kernels around it).
 template <int D, bool DEV, typename S, typename New>
 __global__ void __launch_bounds__(256, 2) fields_add_kernel(S* __restrict__ pops, const New fresh, int N,
                                                          const StepParams p) {
@@ -1677,6 +1681,7 @@ __global__ void __launch_bounds__(256, 2) fields_add_kernel(S* __restrict__ pops
   fresh(n, rho, u, T);
   as_values(rho, u, T);
   const NodeEq<D, DEV> after(k, rho, u, T);
+  constexpr int held = D == 3 && DEV ? 7 : Q / 3;  // rows whose pairs stay in registers
 #pragma unroll
   for (int r = 0; r < Q / 3; ++r) {
 #pragma clang fp contract(off)  // both sides of a difference are rounded
@@ -1684,7 +1689,7 @@ __global__ void __launch_bounds__(256, 2) fields_add_kernel(S* __restrict__ pops
     const double dA = k.rho0 * (w.dA - o.dA), dV = k.rho0 * (w.V2 - o.V2);  // of the terms with constant factors
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      pair_t x = v[3 * r + c];
+      pair_t x = r < held ? v[3 * r + c] : *(const pair_t*)(at + (3 * r + c) * p.sl);
       double df = after.g1[c] * w.A - before.g1[c] * o.A;
       double dg = (after.g1[c] * w.V1 - before.g1[c] * o.V1) + (after.g2[c] * w.A - before.g2[c] * o.A);
       if (DEV) {
