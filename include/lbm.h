@@ -276,9 +276,10 @@ int lbm_batch_get_tile(lbm_batch b, int tile[3]);
 int lbm_batch_set_persistent(lbm_batch b, int on);
 /* The launch form in use (0 or 1), -1 for a NULL batch. */
 int lbm_batch_get_persistent(lbm_batch b);
-/* Autotuner: times every compiled shape with several march-chunk lengths, in
-   both launch forms, over reps launches each and keeps the fastest; *best_ms
-   (may be NULL) gets its time per step.  The timed launches read each box's current populations and
+/* Autotuner: times every compiled shape with several march-chunk lengths, and
+   for D3Q27 with the chunks chosen for the boxes (chunk 0), in both launch
+   forms, over reps launches each and keeps the fastest; *best_ms (may be NULL)
+   gets its time per step.  The timed launches read each box's current populations and
    write the other buffer only, so the states are unchanged.  Synchronous. */
 int lbm_batch_tune(lbm_batch b, int reps, double* best_ms);
 /* Advances every box by n >= 0 steps.  graph_steps > 0: the launches of

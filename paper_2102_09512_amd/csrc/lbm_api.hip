@@ -753,11 +753,12 @@ int batch_capture(Batch* b, int graph_steps) {
   return LBM_OK;
 }
 
-// Supported shared tiles (bx, by) of a lattice.
+// Supported shared tiles (bx, by) of a lattice with several chunk lengths for all
+// boxes, and in D3Q27 with the chunks chosen for them (0), which may be shorter.
 std::vector<lbm::Tile> batch_candidates(int D) {
   std::vector<lbm::Tile> v;
   if (D == 3) {
-    for (int chunk : {4, 8, 16, 32, 64, 128, 256}) {
+    for (int chunk : {0, 4, 8, 16, 32, 64, 128, 256}) {
       v.push_back({64, 4, chunk});
       v.push_back({32, 8, chunk});
       v.push_back({64, 8, chunk});

@@ -177,8 +177,8 @@ hipError_t launch_toggle(const Batch& b, hipStream_t s);
 Tile default_tile(int D, int precision, const int64_t n[3], bool caloric = false);
 int shape_chunk(int D, int precision, const int64_t n[3], int bx, int by, bool caloric = false);
 int default_chunk(int D, const int64_t n[3], int bx, int by);
-// The launch shape (chunk 0) of a batch, and its boxes' chunks in a shape
-// (returns the modelled time, 0 without a model).
+// The launch shape (chunk 0) of a batch, and its boxes' chunks in a shape (returns
+// the modelled time, 0 for D2Q9).
 Tile batch_shape(int D, int precision, const Extent* box, int count);
 double batch_chunks(int D, int precision, const Extent* box, int count, int bx, int by, int* chunk);
 bool tile_supported(int D, int precision, const Tile& t, bool caloric = false);

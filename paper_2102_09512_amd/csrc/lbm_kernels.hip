@@ -1336,49 +1336,48 @@ int shape_chunk(int D, int precision, const int64_t n[3], int bx, int by, bool c
   return own.bx == bx && own.by == by ? own.chunk : default_chunk(D, n, bx, by);
 }
 
-// The modelled time of a batch's launch in a shape, 0 where the shape has no model.
-static double modelled(int D, int precision, int bx, const Load& l) {
-  if (precision == LBM_FP32_DEV) return D == 3 ? kMarch64x8.time(l) : 0.0;
-  if (D == 3) return kMarch3F64[bx == 64 ? 0 : 1].time(l);
-  return bx == 64 ? 0.0 : kRowsF64[bx == 128 ? 0 : 1].time(l);
+// The modelled time of a D3Q27 batch's launch in a shape.
+static double modelled(int precision, int bx, const Load& l) {
+  return precision == LBM_FP32_DEV ? kMarch64x8.time(l) : kMarch3F64[bx == 64 ? 0 : 1].time(l);
 }
 
-// The gain that a batch asks for.  The models have only the mean chunk of the
-// boxes, and D2Q9's rounds follow it closely (1024x64 and 600x1600, two each, FP64:
-// modelled 8% faster with own chunks, measured 8% slower), so that asks for more.
-static bool worth(int D, double time, double base_time, double nodes) {
-  const bool large = nodes > (double)kLargeBox;
-  if (D == 2) return !large && time * kGainLarge < base_time;
-  return time * (large ? kGainLarge : kGain) < base_time;
+static bool worth(double time, double base_time, double nodes) {
+  return time * (nodes > (double)kLargeBox ? kGainLarge : kGain) < base_time;
 }
 
 // March chunks of a batch's boxes in one shape.  A box's own chunk is chosen for
 // a device that it has to itself; in a batch the boxes share the compute units,
-// and a short chunk's prologue is paid by every one of their work-groups.  So the
-// boxes take their own chunks together, where the model finds the launch of all
-// of them faster, or default_chunk.  FP64, us a step with default_chunk in the
+// and a short chunk's prologue is paid by every one of their work-groups.  So
+// D3Q27 boxes take their own chunks together, where the model finds the launch of
+// all of them faster, or default_chunk.  FP64, us a step with default_chunk in the
 // base shape, each box's own chunk whatever the batch, and this rule: 64 boxes of
-// 16^3 123, 202, 120; 48 of 24^3 229, 354, 170; 2 of 160^3 1595, 1742, 1597; one of
-// 20x25x40 30, 15, 15; 85 batches of 1 to 128 boxes are 1.20 times as fast as with
-// default_chunk in the mean, and none is slower.
+// 16^3 123, 202, 119; 48 of 24^3 229, 354, 170; 2 of 160^3 1595, 1742, 1597; one of
+// 20x25x40 30, 15, 15; 57 batches of 1 to 64 boxes are 1.20 times as fast as with
+// default_chunk in the mean, and none is more than 1.1% slower.  D2Q9 boxes have
+// default_chunk: the row model has only their mean chunk, which its rounds follow
+// closely (1024x64 and 600x1600, two each, FP64: modelled 8% faster with own
+// chunks, measured 8% slower), and lbm_batch_tune's chunks start at four rows.
 double batch_chunks(int D, int precision, const Extent* box, int count, int bx, int by, int* chunk) {
   std::vector<int> own(count);
   Load base, fine;
   for (int i = 0; i < count; ++i) {
-    const Tile b{bx, by, default_chunk(D, box[i].n, bx, by)}, t = refined(D, precision, box[i].n, b, false);
+    const Tile b{bx, by, default_chunk(D, box[i].n, bx, by)};
+    chunk[i] = b.chunk;
+    if (D == 2) continue;
+    const Tile t = refined(D, precision, box[i].n, b, false);
     base.add(box[i].n, D, b);
     fine.add(box[i].n, D, t);
-    chunk[i] = b.chunk;
     own[i] = t.chunk;
   }
-  const double base_time = modelled(D, precision, bx, base), time = modelled(D, precision, bx, fine);
-  if (!worth(D, time, base_time, base.nodes)) return base_time;
+  if (D == 2) return 0.0;
+  const double base_time = modelled(precision, bx, base), time = modelled(precision, bx, fine);
+  if (!worth(time, base_time, base.nodes)) return base_time;
   std::copy(own.begin(), own.end(), chunk);
   return time;
 }
 
 // The shape of a batch: the first box's, of the power-of-two rule or, where that
-// is faster for all boxes, of the default.
+// is faster for all boxes, of the default (D3Q27 FP64; elsewhere they are one).
 Tile batch_shape(int D, int precision, const Extent* box, int count) {
   const Tile base = base_tile(D, precision, box[0].n, false), own = default_tile(D, precision, box[0].n);
   if (base.bx == own.bx && base.by == own.by) return Tile{base.bx, base.by, 0};
@@ -1387,7 +1386,7 @@ Tile batch_shape(int D, int precision, const Extent* box, int count) {
   const double time = batch_chunks(D, precision, box, count, own.bx, own.by, chunk.data());
   double nodes = 0.0;
   for (int i = 0; i < count; ++i) nodes += (double)box[i].n[0] * (double)box[i].n[1] * (double)box[i].n[2];
-  const Tile& best = worth(D, time, base_time, nodes) ? own : base;
+  const Tile& best = worth(time, base_time, nodes) ? own : base;
   return Tile{best.bx, best.by, 0};
 }
 
