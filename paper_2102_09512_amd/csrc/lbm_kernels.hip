@@ -1170,14 +1170,68 @@ int default_chunk(int D, const int64_t n[3], int bx, int by) {
   return (int)(chunk < n[1] ? chunk : n[1]);
 }
 
-// Finer models of a launch, for the shapes whose results do not depend on the
+// Two finer models of a launch, for the shapes whose results do not depend on the
 // march chunk (FP64, and 64 x 8 in FP32: one plane in flight, one copy of the
-// plane's arithmetic).  Rounds are counted whole: work-groups of one launch take
-// equally long, so a few of them past a full round cost as much as a round
-// (priced as a fraction of one, FP64 224^3 took 2525 us a step in 784
-// work-groups of 32 x 8 and 56 planes, against 2120 in 224 of 64 x 4).
+// plane's arithmetic).  The first proposes a chunk, the second has to agree.
+//
+// The first: a work-group marches c planes of one tile column and pays p1 planes
+// for its start (launch, the planes next to the chunk, its first loads); one that
+// follows another on its compute unit pays less, p2.  The device holds cap2
+// work-groups of the shape at a time; w2 is what a plane takes them, and w1 what
+// it takes up to cap1 of them, which share no SIMD.  A round that leaves some
+// compute units idle runs a little faster (`idle`; D3Q27, where memory binds).
+struct ShapeModel {
+  int bx, by, cap1, cap2;
+  double w1, w2, p1, p2, idle;
+};
 
-// What the models know of a launch over one or several boxes.
+static double launch_time(const ShapeModel& s, int64_t blocks, double c) {
+  auto filled = [&](int64_t b) { return 1.0 - s.idle * (1.0 - std::max(0.75, (double)b / s.cap2)); };
+  if (blocks <= s.cap2) return (blocks <= s.cap1 ? s.w1 : s.w2) * (c + s.p1) * filled(blocks);
+  const double rounds = (double)blocks / s.cap2;
+  // over many rounds a compute unit takes the next work-group as it gets free
+  if (rounds > 3.0) return s.w2 * ((c + s.p1) + (rounds - 1.0) * (c + s.p2));
+  const int64_t whole = blocks / s.cap2, rest = blocks % s.cap2;
+  double t = s.w2 * ((c + s.p1) + (double)(whole - 1) * (c + s.p2));
+  if (rest) t += (rest <= s.cap1 ? s.w1 : s.w2) * (c + s.p2) * filled(rest);
+  return t;
+}
+
+// One work-group per compute unit.
+static const ShapeModel kShape64x8{64, 8, 256, 256, 1.5, 1.5, 7.0, 6.0, 0.2};
+static const ShapeModel kShapes3F64[] = {{64, 4, 256, 256, 1.0, 1.0, 15.0, 13.0, 0.2},
+                                         {32, 8, 256, 256, 1.02, 1.02, 15.0, 13.0, 0.2}};
+// Two wavefronts per SIMD; two work-groups of a compute unit share SIMDs.
+static const ShapeModel kShape2F64[] = {{128, 1, 256, 1024, 1.03, 1.45, 3.0, 1.5, 0.0},
+                                        {256, 1, 256, 512, 1.06, 1.43, 3.0, 1.5, 0.0}};
+
+// The model's best of the shapes and of the chunks of at most `longest` planes
+// that split the march axis evenly (longer ones gain nothing more).
+static Tile best_tile(const ShapeModel* shapes, int count, const int64_t n[3], int64_t nm, int64_t longest) {
+  Tile best{0, 0, 1};
+  double best_time = 0.0;
+  for (int k = 0; k < count; ++k) {
+    const ShapeModel& s = shapes[k];
+    const int64_t tiles = ((n[0] + s.bx - 1) / s.bx) * (s.by > 1 ? (n[1] + s.by - 1) / s.by : 1);
+    for (int64_t c = 1; c <= longest && c <= nm; ++c) {
+      const int64_t chunks = (nm + c - 1) / c;
+      if ((nm + chunks - 1) / chunks != c) continue;
+      const double t = launch_time(s, tiles * chunks, (double)c);
+      if (!best.bx || t < best_time) {
+        best_time = t;
+        best = Tile{s.bx, s.by, (int)c};
+      }
+    }
+  }
+  return best;
+}
+
+// The second: the first knows nothing of memory, prices a few work-groups past
+// three full rounds as a part of a round, and credits idle compute units too much:
+// FP64 224^3 took 2525 us a step in 784 work-groups of 32 x 8 and 56 planes against
+// 2120 in 224 of 64 x 4, and 227x150x40 358 in 152 of 64 x 4 against 312 in 760.
+//
+// What it knows of a launch over one or several boxes:
 struct Load {
   double blocks = 0, planes = 0, lanes = 0, nodes = 0;  // planes, lanes: of all work-groups
 
@@ -1192,7 +1246,7 @@ struct Load {
   }
 };
 
-// D3Q27: microseconds of a launch whose work-groups march c planes each, one
+// Microseconds of a D3Q27 launch whose work-groups march c planes each, one
 // work-group per compute unit.  A round takes `plane` a plane, and `crowd` more
 // when all compute units march; a launch moves its planes, and `reread` planes
 // next to every chunk, at `cached` to `hbm` microseconds for one plane of all 256
@@ -1210,67 +1264,29 @@ struct MarchModel {
     const double move = cached + (hbm - cached) * std::max(0.0, 1.0 - cache / megabytes);
     const double memory = share * (c + reread) * move / std::sqrt(l.lanes / l.nodes);
     const double march = rounds * c * (plane + crowd * std::min(1.0, share)) + (rounds - 1.0) * start;
-    return (4.0 + start + std::pow(std::pow(memory, 1.5) + std::pow(march, 1.5), 2.0 / 3.0)) * scale;
+    const double both = std::cbrt(memory * std::sqrt(memory) + march * std::sqrt(march));
+    return (4.0 + start + both * both) * scale;
   }
 };
 static const MarchModel kMarch3F64[] = {{64, 4, 8, 4.0, 5.5, 1.3, 2.7, 7.0, 120.0, 3.0, 1.0},
                                         {32, 8, 8, 4.0, 5.5, 1.3, 2.7, 7.0, 120.0, 3.0, 1.05}};
 static const MarchModel kMarch64x8{64, 8, 4, 4.0, 7.0, 0.0, 4.5, 7.4, 160.0, 2.0, 1.0};
 
-// D2Q9, in units of a row: a work-group marches c rows and pays p1 rows for its
-// start; one that follows another on its compute unit pays p2.  The device holds
-// cap2 work-groups of the shape at a time; w2 is what a row takes them, and w1
-// what it takes up to 256 of them, which share no SIMD.
-struct RowModel {
-  int bx, by, cap2;
-  double w1, w2, p1, p2;
-
-  double time(const Load& l) const {
-    const double c = l.planes / l.blocks, whole = std::floor(l.blocks / cap2), rest = l.blocks - whole * cap2;
-    const double last = rest > 0.0 ? (rest <= 256.0 ? w1 : w2) : 0.0;
-    if (whole < 1.0) return last * (c + p1);
-    return w2 * (c + p1) + (w2 * (whole - 1.0) + last) * (c + p2);
-  }
-};
-static const RowModel kRowsF64[] = {{128, 1, 1024, 1.03, 1.45, 3.0, 1.5}, {256, 1, 512, 1.06, 1.43, 3.0, 1.5}};
-
-// Of the shapes' chunks of at most `longest` planes that split the march axis
-// evenly (longer ones gain nothing more), the one that the model gives the
-// shortest time, if that is shorter than `base`'s by the factor `gain`; else base.
-// 1.07 up to 4 M nodes, where of 974 boxes with another choice than base one was
-// slower than base by more than 1.5% (2.0%), and the mean gain was 1.39 (D3Q27
-// FP64), 1.17 (64 x 8) and 1.31 (D2Q9).  Larger boxes are bound by memory more
-// than the models know: D3Q27 asks for 1.15 (with 1.07, 9 of 142 lost up to
-// 12%; with 1.15 none of 40), and D2Q9 keeps base (31 of 327 lost up to 12%).
-constexpr int64_t kLargeBox = 4000000;
-constexpr double kGain = 1.07, kGainLarge = 1.15;
-
-template <typename Model>
-static Tile refine(const Model* shapes, int count, const int64_t n[3], int D, int64_t longest, double gain,
-                   const Tile& base) {
-  const int64_t nm = D == 3 ? n[2] : n[1];
-  auto time = [&](const Model& s, int64_t c) {
-    Load l;
-    l.add(n, D, Tile{s.bx, s.by, (int)c});
-    return s.time(l);
-  };
-  Tile best = base;
-  double best_time = -1.0, base_time = -1.0;
-  for (int k = 0; k < count; ++k) {
-    const Model& s = shapes[k];
-    if (s.bx == base.bx && s.by == base.by) base_time = time(s, base.chunk);
-    for (int64_t c = 1; c <= longest && c <= nm; ++c) {
-      const int64_t chunks = (nm + c - 1) / c;
-      if ((nm + chunks - 1) / chunks != c) continue;
-      const double t = time(s, c);
-      if (best_time < 0.0 || t < best_time) {
-        best_time = t;
-        best = Tile{s.bx, s.by, (int)c};
-      }
-    }
-  }
-  return best_time * gain < base_time ? best : base;
+// The second model's time of a launch in a shape.
+static double modelled(int precision, int bx, const Load& l) {
+  return precision == LBM_FP32_DEV ? kMarch64x8.time(l) : kMarch3F64[bx == 64 ? 0 : 1].time(l);
 }
+
+// A proposal is taken where the second model finds it no slower than the base:
+// of 1937 D3Q27 boxes up to 4.2 M nodes with another choice than the base, over
+// both schemes, open and periodic axes and both caloric laws, four are slower by
+// more than 2.5% (at most 6%), and the mean gain is 1.43 (FP64) and 1.16 (64 x 8);
+// without the second model nine, by up to 16%.  Larger boxes have to gain 1.05: of
+// 53 none is slower (without the second model 17, by up to 16%).  D2Q9's first
+// model has none slower of 978 boxes up to 4 M nodes, at a mean gain of 1.62, and
+// 15 of 100 larger ones, by up to 19%, which keep the base.
+constexpr int64_t kLargeBox = 4000000;
+constexpr double kGainLarge = 1.05;
 
 // Default launch shape and march chunk (32 x 16 tiles, the 512-thread shape
 // with the smallest halo ring, measured 10% slower than 64 x 8 at 256^3 FP32
@@ -1316,15 +1332,19 @@ static Tile base_tile(int D, int precision, const int64_t n[3], bool caloric) {
 // base, refined over its own shape, or over all shapes of its lattice.
 static Tile refined(int D, int precision, const int64_t n[3], const Tile& base, bool all_shapes) {
   const bool large = n[0] * n[1] * n[2] > kLargeBox;
-  if (D == 3) {
-    const double gain = large ? kGainLarge : kGain;
-    if (precision == LBM_FP32_DEV)
-      return base.bx == 64 && base.by == 8 ? refine(&kMarch64x8, 1, n, D, 256, gain, base) : base;
-    if (all_shapes) return refine(kMarch3F64, 2, n, D, 256, gain, base);
-    return refine(&kMarch3F64[base.bx == 64 ? 0 : 1], 1, n, D, 256, gain, base);
+  if (D == 2) {
+    if (precision == LBM_FP32_DEV || large || base.bx < 128) return base;
+    return best_tile(&kShape2F64[base.bx == 128 ? 0 : 1], 1, n, n[1], 32);
   }
-  if (precision == LBM_FP32_DEV || large || base.bx < 128) return base;
-  return refine(&kRowsF64[base.bx == 128 ? 0 : 1], 1, n, D, 32, kGain, base);
+  const bool wide = base.bx == 64 && base.by == 8;
+  if (precision == LBM_FP32_DEV && !wide) return base;
+  const Tile t = precision == LBM_FP32_DEV ? best_tile(&kShape64x8, 1, n, n[2], 256)
+                 : all_shapes             ? best_tile(kShapes3F64, 2, n, n[2], 256)
+                                          : best_tile(&kShapes3F64[base.bx == 64 ? 0 : 1], 1, n, n[2], 256);
+  Load before, after;
+  before.add(n, D, base);
+  after.add(n, D, t);
+  return modelled(precision, t.bx, after) * (large ? kGainLarge : 1.0) <= modelled(precision, base.bx, before) ? t : base;
 }
 
 Tile default_tile(int D, int precision, const int64_t n[3], bool caloric) {
@@ -1336,13 +1356,8 @@ int shape_chunk(int D, int precision, const int64_t n[3], int bx, int by, bool c
   return own.bx == bx && own.by == by ? own.chunk : default_chunk(D, n, bx, by);
 }
 
-// The modelled time of a D3Q27 batch's launch in a shape.
-static double modelled(int precision, int bx, const Load& l) {
-  return precision == LBM_FP32_DEV ? kMarch64x8.time(l) : kMarch3F64[bx == 64 ? 0 : 1].time(l);
-}
-
 static bool worth(double time, double base_time, double nodes) {
-  return time * (nodes > (double)kLargeBox ? kGainLarge : kGain) < base_time;
+  return time * (nodes > (double)kLargeBox ? 1.15 : 1.07) < base_time;
 }
 
 // March chunks of a batch's boxes in one shape.  A box's own chunk is chosen for
@@ -1351,12 +1366,11 @@ static bool worth(double time, double base_time, double nodes) {
 // D3Q27 boxes take their own chunks together, where the model finds the launch of
 // all of them faster, or default_chunk.  FP64, us a step with default_chunk in the
 // base shape, each box's own chunk whatever the batch, and this rule: 64 boxes of
-// 16^3 123, 202, 119; 48 of 24^3 229, 354, 170; 2 of 160^3 1595, 1742, 1597; one of
-// 20x25x40 30, 15, 15; 57 batches of 1 to 64 boxes are 1.20 times as fast as with
-// default_chunk in the mean, and none is more than 1.1% slower.  D2Q9 boxes have
-// default_chunk: the row model has only their mean chunk, which its rounds follow
-// closely (1024x64 and 600x1600, two each, FP64: modelled 8% faster with own
-// chunks, measured 8% slower), and lbm_batch_tune's chunks start at four rows.
+// 16^3 123, 202, 116; 48 of 24^3 229, 354, 229; 2 of 160^3 1610, 1742, 1385; one of
+// 20x25x40 30, 15, 15; 57 batches of 1 to 64 boxes are 1.22 times as fast as with
+// default_chunk in the mean, and none is slower.  D2Q9 boxes have
+// default_chunk: own chunks made a batch of 1024x64 and 600x1600, two each, 8%
+// slower in FP64, and lbm_batch_tune's chunks start at four rows.
 double batch_chunks(int D, int precision, const Extent* box, int count, int bx, int by, int* chunk) {
   std::vector<int> own(count);
   Load base, fine;

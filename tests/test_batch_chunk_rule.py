@@ -44,7 +44,7 @@ def test_shared_device_keeps_default_chunks(boxes):
 
 
 def test_many_small_boxes_do_not_pay_a_prologue_per_plane():
-    _, chunks = _batch([(24, 24, 24)] * 48, 0)  # 354 us with one-plane chunks, 170 with these
+    _, chunks = _batch([(24, 24, 24)] * 48, 0)  # 354 us with one-plane chunks, 229 with these
     assert min(chunks) >= 4
 
 
