@@ -162,8 +162,8 @@ int lbm_moments(lbm_handle h, double* rho, double* u, double* T, int mem);
    *out (host): the totals of Eqs. (3)-(5) and the statistics of Sec. III.D
    listed at lbm_diag.  Sets the handle's instability flag when a node is
    non-finite or has rho <= 0 or T <= 0 (lbm_step then returns
-   LBM_EUNSTABLE).  Allocates the partial sums on first use.  LBM_EINVAL on a NULL argument, LBM_ESTATE before
-   lbm_init_fields. */
+   LBM_EUNSTABLE).  Allocates the partial sums on first use.  LBM_EINVAL on a
+   NULL argument, LBM_ESTATE before lbm_init_fields. */
 int lbm_diagnostics(lbm_handle h, lbm_diag* out);
 /* lbm_diagnostics for callers that cannot allocate device memory (code
    under HIP graph capture, tight serving loops, harnesses that forbid

@@ -40,8 +40,11 @@ extern "C" {
 typedef struct lbm_nn_ctx* lbm_nn;
 
 /* layers >= 1; channels[0..layers]; dims of the grid the network runs on.
-   Allocates parameters, gradients, Adam moments and the activations of one
-   sample (about 200 bytes per node). */
+   Allocates parameters, gradients, Adam moments, the activations of one sample
+   (352 bytes per node and 64 for every hidden layer), and the partial sums of
+   the weight gradients (per layer 28 c_in c_out floats for each of at most 256
+   work-groups, 512 where one side has at most 8 channels; fewer on grids below
+   64^3 nodes; at most 117 MB in all). */
 int lbm_nn_create(lbm_nn* out, int layers, const int* channels, const int64_t dims[3]);
 int lbm_nn_destroy(lbm_nn net);
 int lbm_nn_set_stream(lbm_nn net, void* hip_stream);

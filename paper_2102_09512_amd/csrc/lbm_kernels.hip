@@ -678,8 +678,7 @@ __global__ void __launch_bounds__(256) init_kernel(const double* __restrict__ rh
 }
 
 // ---------------------------------------------------------------------------
-// Moments of the stored populations (no streaming), FP64 fields
-// fields: rho, ux, uy, uz, T, rhoE (each N)
+// Moments of the stored populations (no streaming), FP64
 // ---------------------------------------------------------------------------
 
 // The Q (f, g) pairs of the node whose slot-0 pair is at src.
@@ -1294,7 +1293,7 @@ constexpr double kGainLarge = 1.05;
 // lattice.
 // D3Q27: the shape with the lowest march_cost at its best power-of-two chunk;
 // for FP64, and for 64 x 8 (the only 512-thread shape that fits 256 registers
-// without spilling), refined by the model.  The 256-thread FP32 shapes keep two
+// without spilling), refined by the models.  The 256-thread FP32 shapes keep two
 // planes in flight through a plane loop unrolled three times; the compiler fuses
 // products and sums a little differently in each copy, so there the rounding of a
 // node follows the chunk, and a different chunk moves the results of long runs,
@@ -1304,7 +1303,7 @@ constexpr double kGainLarge = 1.05;
 // 256^3 (9% faster than 64 x 4 / 256 there).
 // D2Q9: rows of 128, or of 256 from 1024 nodes per row (FP32: 9% faster at
 // 4096^2, even at 1024^2 and 2048^2; FP64 at 1024^2: 4% faster), FP64 refined by
-// the model.  FP32 keeps two rows in flight, so its chunks stay as they are too.
+// the first model.  FP32 keeps two rows in flight, so its chunks stay as they are too.
 // Microseconds a step, base and choice: FP64 20x25x40 64x4/4 31.4, 32x8/1 14.6;
 // 190x131x110 64x4/16 600, 64x4/55 555; 800x4 128x1/4 11.2, 128x1/1 6.2; 300^2
 // 128x1/4 15.1, 128x1/1 10.7; FP32 190x131x110 64x8/32 346, 64x8/22 296.

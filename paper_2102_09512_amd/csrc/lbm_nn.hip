@@ -441,13 +441,13 @@ __global__ void __launch_bounds__(64 * kW) conv_narrow_kernel(const __bf16* __re
 // shifts.  Wave w of a half owns seven slots (the three dx taps of two (dy, dz)
 // pairs and one more; see the loop) and keeps their sums in registers across
 // the tiles.
-// What binds is not the matrix cores but what surrounds them: a work-group's
-// partials (114 KB at 32 channels) are as much as the tiles that it reads, so
-// the halves add theirs in LDS and one work-group per compute unit writes;
-// the next tile's input is requested before the products of the present one;
-// and two neighbouring nodes of a channel go to LDS as one 4-byte word.
-// 64^3, 32 channels: 27.5 us (32.2 us with 512 work-groups of one half each,
-// staged and written without these).
+// What binds is not the matrix cores but what surrounds them.  With 512
+// work-groups of one half each at 64^3, a work-group's partials (114 KB at 32
+// channels) were nearly as much as the two tiles that it reads (137 KB); the halves
+// add theirs in LDS and one work-group per compute unit writes, for four tiles.
+// The next tile's input is requested before the products of the present one, and
+// two neighbouring nodes of a channel go to LDS as one 4-byte word.  64^3, 32
+// channels: 27.5 us (32.2 us in the former launch, without these).
 constexpr int kGX = 32, kGY = 4, kGZ = 2;
 constexpr int kGHY = kGY + 2, kGHZ = kGZ + 2, kGHX = kGX + 2;
 constexpr int kGRow = 40;                           // halo row: 34 nodes, padded to a 16-byte multiple
